@@ -20,6 +20,9 @@
 #include "pdssm_device.h"
 #include "pdssm_select.h"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace pdssm {
 
 namespace {
@@ -282,6 +285,36 @@ __device__ __forceinline__ float2 diag_gen(float m, float p) {
     return make_float2(r * c, r * s);
 }
 
+// The same for |m| < kGenMag and |p| < kGenPhase in straight-line code (a
+// kernel with 256 accumulators cannot afford sincosf's branch for large
+// arguments in its epilogue).  exp(-m) = 2^t 2^u, t + u = -m log2(e) in two
+// parts; the reciprocal of 1 + exp(-m) by the hardware's and one Newton step;
+// the phase reduced by multiples k of pi/2 in three parts (k < 2^13: the first
+// difference is exact), sin and cos by least-maximum polynomials on
+// [-pi/4, pi/4] (relative errors 4e-9 and 1e-10, below fp32 rounding).
+constexpr float kGenMag = 80.f, kGenPhase = 8192.f;
+__device__ __forceinline__ float2 diag_gen_small(float m, float p) {
+    const float t = m * -0x1.715476p+0f;
+    const float u = fmaf(m, -0x1.4ae0cp-26f, fmaf(m, -0x1.715476p+0f, -t));
+    const float e = __builtin_amdgcn_exp2f(t);
+    const float d = 1.f + fmaf(e, u * 0x1.62e430p-1f, e);
+    const float r0 = __builtin_amdgcn_rcpf(d);
+    const float r = fmaf(fmaf(-d, r0, 1.f), r0, r0);
+    const float k = rintf(p * 0x1.45f306p-1f);
+    float x = fmaf(-k, 0x1.921fb6p+0f, p);
+    x = fmaf(k, 0x1.777a5cp-25f, x);
+    x = fmaf(k, 0x1.ee59dap-50f, x);
+    const float x2 = x * x;
+    const float s = fmaf(x * x2, fmaf(x2, fmaf(x2, -0x1.994e5cp-13f, 0x1.11076p-7f), -0x1.555546p-3f), x);
+    const float c = fmaf(x2 * x2, fmaf(x2, fmaf(x2, 0x1.9a020ap-16f, -0x1.6c0c8ap-10f), 0x1.55554ap-5f),
+                         fmaf(-0.5f, x2, 1.f));
+    const int q = (int)k;
+    const uint32_t flip_s = (uint32_t)(q & 2) << 30, flip_c = (uint32_t)((q + 1) & 2) << 30;
+    const float ss = __uint_as_float(__float_as_uint(q & 1 ? c : s) ^ flip_s);
+    const float cc = __uint_as_float(__float_as_uint(q & 1 ? s : c) ^ flip_c);
+    return make_float2(r * cc, r * ss);
+}
+
 template <int BM>
 __global__ __launch_bounds__(512) void k_project_dma(ProjectArgs a) {
     using C = RouteDma<BM>;
@@ -453,6 +486,485 @@ __global__ __launch_bounds__(512) void k_project_dma(ProjectArgs a) {
     }
 }
 
+// ------------------------------------------------------------------ k_project_wide
+// The same product for problems that fill the chip with 256 x 256 tiles and
+// are mostly projections.  Four waves, one per SIMD, each 128 x 128 with its
+// 256 accumulators in AGPRs: per slice of 64 the operands cost 128 KB of LDS
+// reads a workgroup against 192 KB with eight waves of 128 x 64.  Slices come
+// as whole 128-byte lines (half lines reach half the L2 rate) through a ring of
+// five 32 KB units, so that one and a half slices are in flight while one is
+// multiplied; one barrier per 64 matrix instructions of a wave, every other
+// instruction of the slice set between them.  The workgroups are persistent
+// and run on into the next tile's slices: its loads are in flight during the
+// epilogue, which writes (re, im) pairs straight from the accumulators (the
+// weights' rows are permuted in LDS so that a pair's two columns fall to one
+// lane) without staging or waiting.
+//
+// Bound: the matrix cores at the clock that the card's power limit leaves
+// (about 1.8 GHz of 2.4 with normal data); of the cycles of a launch at
+// hybrid-lm, 66% are matrix instructions' own, 14% the barriers and operand
+// reads, 9% the loads and 11% the epilogue.  Measured against eight waves with
+// slices of 32: B8 L4096 d 4096, 26624 columns 8150 -> 5700 us (1250 TFLOP/s;
+// the vendor library's plain bf16 product of these sizes 1520), B16 L2048
+// d 1024, 6400 columns 640 -> 480 us.  Without the L2 prefetch the former
+// takes 8% more; with loads issued two at a time 5% more.
+struct WideProj {
+    static constexpr int BM = 256, BN = 256, BK = 64;
+    static constexpr int ROWB = BK * 2;           // bytes of a row's slice: one 128-byte line
+    static constexpr int UNIT = BM * ROWB;        // a ring unit: 256 rows of u or of the weights, 32 KB
+    static constexpr int RING = 5;                // units; slice s of u is unit 2s % 5, of the weights (2s + 1) % 5
+    static constexpr int PER_WAVE = BM / 8 / 2;   // loads (8 rows each) per wave per slice
+    static constexpr int GM = 8;                  // token tiles of a group (see tile_at)
+    static constexpr size_t LDS = (size_t)RING * UNIT;
+    static_assert(BM == BN && LDS <= 160 * 1024, "fits the LDS of a CU");
+};
+
+// 8 bytes at byte offset voff of the buffer, which no later read of this
+// kernel wants: kept out of the L2's way.
+__device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t r, uint32_t voff, float2 v) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(v.x), __float_as_uint(v.y)}, r, voff, 0, kLoadStream);
+}
+
+// A tile of the product: 256 tokens x 256 columns, the columns as two halves
+// of up to 128 (one per wave column).  Routing halves hold whole heads when
+// K <= 128; a larger head spans both halves of its tile.
+struct WideTile {
+    int m0;      // first token
+    int kind;    // -1: routing; else the projection's index
+    int r0;      // first weight row of half 0
+    int nt;      // column tile
+    int hc;      // weight rows of a full half: half 1 starts at r0 + hc
+    int rows;    // rows of the weight matrix
+    int h0;      // routing: first head of half 0
+};
+
+__device__ __forceinline__ int wide_hph(int K) { return K <= 128 ? 128 / K : 1; }  // heads per half (K > 128: per tile)
+
+__host__ __device__ inline int wide_col_tiles(int H, int K, int N, bool route, int nproj) {
+    const int per = K <= 128 ? 2 * (128 / K) : 1;
+    return (route ? (H + per - 1) / per : 0) + nproj * ((2 * H * N + 255) / 256);
+}
+
+__device__ __forceinline__ WideTile wide_tile(const ProjectArgs& a, int nt, int mt) {
+    WideTile t;
+    t.m0 = mt * WideProj::BM;
+    t.nt = nt;
+    const int hph = wide_hph(a.K), per = a.K <= 128 ? 2 * hph : 1;
+    const int NTr = a.S ? (a.H + per - 1) / per : 0;
+    if (nt < NTr) {
+        t.kind = -1;
+        t.h0 = nt * per;
+        t.r0 = t.h0 * a.K;
+        t.hc = a.K <= 128 ? hph * a.K : 128;
+        t.rows = a.H * a.K;
+    } else {
+        const int R = 2 * a.H * a.N, NTp = (R + 255) / 256, j = nt - NTr;
+        t.kind = j / NTp;
+        t.r0 = (j - t.kind * NTp) * 256;
+        t.hc = 128;
+        t.rows = R;
+        t.h0 = 0;
+    }
+    return t;
+}
+
+__global__ __launch_bounds__(256, 1) void k_project_wide(ProjectArgs a) {
+    using C = WideProj;
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int wm = wv >> 1, wn = wv & 1;
+    const int l32 = lane & 31, hf = lane >> 5;
+    const int HK = a.H * a.K, R = 2 * a.H * a.N;
+    const int NT = wide_col_tiles(a.H, a.K, a.N, a.S != nullptr, a.nproj), MT = (a.T + C::BM - 1) / C::BM;
+    const int total = NT * MT;
+    // this workgroup's tiles: every (gridDim / 8)-th of its XCD's range
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, nslot = gridDim.x >> 3;
+    const int lo = (int)((long long)total * xcd / 8), hi = (int)((long long)total * (xcd + 1) / 8);
+    int tc = lo + slot;  // tile being multiplied
+    if (tc >= hi) return;
+    const int nsl = (a.Dm + C::BK - 1) / C::BK;
+    const bool half_tail = a.Dm % C::BK != 0;  // Dm is a multiple of 32: the last slice has two of its four steps
+
+    auto tile_at = [&](int t) {
+        const int per = C::GM * NT, g = t / per, rem = t - g * per;
+        const int gm = min(C::GM, MT - g * C::GM);
+        const int nt = rem / gm;
+        return wide_tile(a, nt, g * C::GM + rem - nt * gm);
+    };
+
+    // ---- loads: waves 0, 1 bring a slice's 256 rows of u, waves 2, 3 those of
+    // the weights, 8 rows of 128 bytes an instruction.  Place r's 16-byte chunk c
+    // lies at chunk position c ^ swz(r): any 8 (16) consecutive rows at one
+    // chunk fall on distinct banks of 32 (64).
+    const uint32_t row_bytes = (uint32_t)a.Dm * 2;
+    int tl = tc;             // tile of the next slice to load
+    int ls = 0;              // that slice
+    int lunit = wv < 2 ? 0 : 1;  // the ring unit it goes to
+    __amdgpu_buffer_rsrc_t rsrc;
+    uint32_t voff[C::PER_WAVE];
+    // past the last tile the descriptor is empty: the loads go on, as zeros
+    auto point = [&](int t) {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // recomputed here, not kept in registers across the products
+        if (t >= hi) {
+            rsrc = row_block(a.u, 0);
+            return;
+        }
+        const WideTile w = tile_at(t);
+        const bool tok = wv < 2;
+        const uint16_t* base = tok ? a.u : w.kind < 0 ? a.S : a.W[w.kind];
+        const uint32_t rows = (uint32_t)(tok ? a.T : w.rows);
+        const int first = tok ? w.m0 + (wv & 1) * 128 : w.r0 + (wv & 1) * w.hc;
+        rsrc = row_block(base, rows * row_bytes);
+        // place 8 i + ln / 8 of the wave's 128 holds row 8 i + ln / 8 of u; of the
+        // weights, places 64 g + 32 e + l hold row 64 g + 2 l + e
+        const uint32_t at = (uint32_t)first * row_bytes + (uint32_t)((ln >> 3) << (tok ? 0 : 1)) * row_bytes;
+        const uint32_t last = (rows - 1) * row_bytes;
+#pragma unroll
+        for (int i = 0; i < C::PER_WAVE; ++i) {
+            const int wr = 64 * (i >> 3) + 16 * (i & 3) + (i >> 2 & 1);
+            voff[i] = min(at + (uint32_t)(tok ? 8 * i : wr) * row_bytes, last) +
+                      16u * (uint32_t)((ln & 7) ^ ((ln >> 3) & 7) ^ (i & 1));
+        }
+    };
+    // a half tail slice holds 64 bytes of each row: its upper chunks start past
+    // every descriptor (buffers below 2 GiB) and arrive as zeros
+    const uint32_t gone = ((lane & 7) ^ (lane >> 3)) & 4 ? 0x80000000u : 0u;
+    uint32_t skip = half_tail && nsl == 1 ? gone : 0u;
+    auto issue = [&](int i) {
+        load_lds16(rsrc, lds + lunit * C::UNIT + ((wv & 1) * C::PER_WAVE + i) * 1024, voff[i] | skip,
+                   (uint32_t)ls * C::ROWB);
+    };
+    auto next_unit = [](int u) { return u >= C::RING - 2 ? u - (C::RING - 2) : u + 2; };
+    auto advance = [&]() {
+        lunit = next_unit(lunit);
+        if (tl < hi) ++ls;
+        if (ls == nsl) {
+            ls = 0;
+            tl += nslot;
+            point(tl);
+        }
+        skip = half_tail && ls == nsl - 1 ? gone : 0u;
+    };
+    auto issue_all = [&]() {
+#pragma unroll
+        for (int i = 0; i < C::PER_WAVE; ++i) issue(i);
+        advance();
+    };
+
+    // ---- L2 prefetch: the tiles in flight on an XCD share their rows (GM token
+    // tiles x 32 / GM column tiles), so each workgroup touches a share of its
+    // tile's lines kAhead slices before they are loaded: waves 0, 1 a quarter of
+    // the tokens' lines, waves 2, 3 an eighth of the weights'.  One load a slice.
+    constexpr int kAhead = 3;
+    int pt = tl, ps = 0;
+    __amdgpu_buffer_rsrc_t prsrc;
+    uint32_t pvoff;
+    auto ppoint = [&](int t) {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        prsrc = row_block(a.u, 0);
+        pvoff = 0;
+        if (t >= hi) return;
+        const WideTile w = tile_at(t);
+        const bool tok = wv < 2;
+        const uint16_t* base = tok ? a.u : w.kind < 0 ? a.S : a.W[w.kind];
+        const uint32_t rows = (uint32_t)(tok ? a.T : w.rows);
+        const int rr = tok ? 64 * (w.nt & 3) + 32 * (wv & 1) + (ln & 31)
+                           : 32 * (w.m0 / C::BM & 7) + 16 * (wv & 1) + (ln & 15);
+        const int first = tok ? w.m0 + rr : rr < 128 ? w.r0 + rr : w.r0 + w.hc + rr - 128;
+        prsrc = row_block(base, rows * row_bytes);
+        pvoff = min((uint32_t)first * row_bytes, (rows - 1) * row_bytes);
+    };
+    uint32_t pf = 0;
+    auto padvance = [&]() {
+        if (pt < hi && ++ps == nsl) {
+            ps = 0;
+            pt += nslot;
+            ppoint(pt);
+        }
+    };
+
+    // ---- operand reads: wave (wm, wn) multiplies tokens 128 wm .. and columns
+    // 128 wn ..; a lane's columns of products 2jj and 2jj + 1 are the pair
+    // 64 jj + 2 l32, + 1 (real and imaginary part of one entry)
+    const int swz = (l32 & 7) ^ ((l32 >> 3) & 1);
+    uint32_t xu[4], xw[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        xu[kk] = (uint32_t)(wm * 128 + l32) * C::ROWB + 16u * (uint32_t)((2 * kk + hf) ^ swz);
+        xw[kk] = (uint32_t)(wn * 128 + l32) * C::ROWB + 16u * (uint32_t)((2 * kk + hf) ^ swz);
+    }
+    struct Frag {
+        bf16x8 u[4], w[4];
+    } f[2];
+    auto rd_u = [&](int unit, int kk, int i) {
+        return *reinterpret_cast<const bf16x8*>(lds + unit * C::UNIT + xu[kk] + 32 * i * C::ROWB);
+    };
+    auto rd_w = [&](int unit, int kk, int j) {
+        return *reinterpret_cast<const bf16x8*>(lds + unit * C::UNIT + xw[kk] + 32 * j * C::ROWB);
+    };
+    // acc[i][j]: lane = column, register r = token 32 i + 8 (r / 4) + 4 hf + r % 4
+    f32x16 acc[4][4];
+    // one step of 16: 16 products on fragment set cur and, between them, the
+    // next step's eight operand reads and half (1: first, 2: second) of a
+    // slice's loads; the second half moves the cursors on
+    auto step = [&](auto cur_, int uu, int uw, int rkk, auto loads_) {
+        constexpr int cur = decltype(cur_)::value;
+        constexpr int LOADS = decltype(loads_)::value;
+        Frag& n = f[cur ^ 1];
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+            const int i = m >> 2, j = m & 3;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[cur].u[i], f[cur].w[j], acc[i][j], 0, 0, 0);
+            if (m == 0) n.u[0] = rd_u(uu, rkk, 0);
+            if (m == 1) n.w[0] = rd_w(uw, rkk, 0);
+            if (m == 2) n.w[1] = rd_w(uw, rkk, 1);
+            if (m == 3) n.w[2] = rd_w(uw, rkk, 2);
+            if (m == 4) n.w[3] = rd_w(uw, rkk, 3);
+            if (m == 5) n.u[1] = rd_u(uu, rkk, 1);
+            if (m == 7) n.u[2] = rd_u(uu, rkk, 2);
+            if (m == 9) n.u[3] = rd_u(uu, rkk, 3);
+            if constexpr (LOADS == 1)
+                if (m % 2 == 0) issue(m / 2);
+            if constexpr (LOADS == 2) {
+                if (m < 8) issue(m + C::PER_WAVE / 2);
+                if (m == 9) {
+                    asm volatile("" ::"v"(pf));  // a slice old
+                    pf = __builtin_amdgcn_raw_buffer_load_b32(prsrc, pvoff, (uint32_t)ps * C::ROWB, 0);
+                }
+                if (m == 11) advance();
+                if (m == 13) padvance();
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    using c0 = std::integral_constant<int, 0>;
+    using c1 = std::integral_constant<int, 1>;
+    using c2 = std::integral_constant<int, 2>;
+
+    // ---- prologue: slice 0 (and 1 of u) of the flattened sequence, then the
+    // first half of the next
+    auto issue_half = [&]() {
+#pragma unroll
+        for (int i = 0; i < C::PER_WAVE / 2; ++i) issue(i);
+    };
+    point(tl);
+    issue_all();
+    if (wv < 2) {
+        issue_all();
+        issue_half();
+        wait_vmcnt<3 * C::PER_WAVE / 2>();
+    } else {
+        issue_half();
+        wait_vmcnt<C::PER_WAVE / 2>();
+    }
+    ppoint(pt);
+    for (int i = 0; i < 2 + kAhead; ++i) padvance();
+    barrier_no_fence();
+    int uu = 0, uw = 1;  // ring units of the slice being multiplied
+    f[0].u[0] = rd_u(uu, 0, 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f[0].w[j] = rd_w(uw, 0, j);
+#pragma unroll
+    for (int i = 1; i < 4; ++i) f[0].u[i] = rd_u(uu, 0, i);
+
+    bool stores = false;  // at least 63 stores follow the last loads issued
+    for (;;) {
+        const WideTile w = tile_at(tc);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        // every read of this slice's units has returned and the next slice has
+        // arrived, for every wave: the units may be loaded again.  Waves 0, 1
+        // may have the u slice after the next in flight (and with 63 stores
+        // after it, the next has been answered: answers come in order); the last
+        // prefetch may be in flight.
+        auto turn = [&]() {
+            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+            if (wv >= 2) wait_vmcnt<1>();
+            else if (!stores) wait_vmcnt<C::PER_WAVE + 1>();
+            stores = false;
+            barrier_no_fence();
+        };
+        // the slice's last step: the next slice's first reads, and the loads of
+        // a later one into the units just finished
+        int done_w = 0;  // the unit that waves 0, 1 are loading u into
+        auto last = [&](auto cur) {
+            done_w = uw;
+            const int nu = next_unit(uu), nw = next_unit(uw);
+            step(cur, nu, nw, 0, c1{});
+            uu = nu;
+            uw = nw;
+        };
+        for (int s = 0; s < nsl; ++s) {
+            step(c0{}, uu, uw, 1, c2{});
+            step(c1{}, uu, uw, 2, c0{});
+            step(c0{}, uu, uw, 3, c0{});
+            turn();
+            last(c1{});
+        }
+        // ---- epilogue.  Lane-dependent addresses are formed here from an opaque
+        // copy of the lane, not kept in registers across the products.
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int l32 = ln & 31, hf = ln >> 5;
+        const int tb = w.m0 + wm * 128;             // first token of this wave's block
+        const int nt = max(0, min(128, a.T - tb));  // its tokens
+        const int cr = w.r0 + wn * w.hc;            // its first weight row
+        if (w.kind >= 0) {
+            // a projection: rows of [T, H*2N] floats, a lane's pair of columns
+            // one 8-byte store (32 lanes: 256 contiguous bytes of a row), never
+            // waited for.  The descriptor ends after the block's last token and
+            // a lane past the last column starts beyond it: those stores drop.
+            const int ncol = min(128, R - cr);
+            const bool gen = a.kind[w.kind] == kProjGen;
+            float* out = a.out[w.kind] + (size_t)tb * R + cr;
+            const uint64_t ob = reinterpret_cast<uint64_t>(out);
+            const __amdgpu_buffer_rsrc_t ro = row_block(
+                reinterpret_cast<void*>((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(ob >> 32)) << 32 |
+                                        (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)ob)),
+                __builtin_amdgcn_readfirstlane(nt ? (uint32_t)((nt - 1) * R + ncol) * 4 : 0));
+            uint32_t at[2];
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+                at[jj] = 64 * jj + 2 * l32 < ncol ? (uint32_t)(4 * hf * R + 64 * jj + 2 * l32) * 4 : 0xc0000000u;
+            float most = 0.f;  // largest |m| / kGenMag and |p| / kGenPhase seen
+            auto emit = [&](auto f) {
+                uint32_t v0 = at[0], v1 = at[1], step = (uint32_t)R * 4;
+                asm volatile("" : "+s"(step));  // row offsets formed here, not kept across the products
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        store_pair(ro, v0, f(acc[i][0][r], acc[i][1][r]));
+                        store_pair(ro, v1, f(acc[i][2][r], acc[i][3][r]));
+                        v0 += (r & 3) == 3 ? 5 * step : step;  // token 32 i + 8 (r / 4) + r % 4 + 4 hf
+                        v1 += (r & 3) == 3 ? 5 * step : step;
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+            };
+            if (gen)
+                emit([&](float m, float p) {
+                    most = fmaxf(most, fmaxf(fabsf(m) * (1.f / kGenMag), fabsf(p) * (1.f / kGenPhase)));
+                    return diag_gen_small(m, p);
+                });
+            const bool large = __any(most >= 1.f);  // NaN passes through diag_gen_small unharmed
+            if (!gen || large) emit([](float m, float p) { return make_float2(m, p); });
+            if (large)  // the general form, on the values just stored, each by its own lane
+#pragma unroll 1
+                for (int e = 0; e < 128; ++e) {
+                    const int t = 32 * (e >> 5) + 8 * (e >> 3 & 3) + 4 * hf + (e >> 1 & 3), c = 64 * (e & 1) + 2 * l32;
+                    if (t >= nt || c >= ncol) continue;
+                    float2* o = reinterpret_cast<float2*>(out + (size_t)t * R + c);
+                    const float2 v = *o;
+                    *o = diag_gen(v.x, v.y);
+                }
+            stores = nt == 128 && ncol == 128;
+        } else {
+            // routing: 32 tokens x 64 columns at a time through a staging area
+            // of this wave in the ring unit that half of a later u slice went to
+            // (loaded once more afterwards)
+            wait_vmcnt<0>();
+            barrier_no_fence();
+            unsigned char* stg = lds + done_w * C::UNIT + wv * (C::UNIT / 4);
+            const int hd0 = a.K <= 128 ? w.h0 + wn * wide_hph(a.K) : w.h0;  // this half's first head
+            const int ncol = a.K <= 128 ? min(wide_hph(a.K), a.H - hd0) * a.K : wn == 0 ? 128 : a.K - 128;
+            const bool fresh = a.K <= 128 || wn == 0;  // else the second half of a head: nothing chosen yet
+            const int rq = ln >> 4, q = ln & 15;       // rows rq, rq + 4, ...; columns 4q .. 4q + 3
+            // 16-byte chunk q of a staged row lies at chunk position q ^ (row % 16)
+            float bv[4];
+            int best[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                int k = 0, hd = hd0;
+                bv[i] = -INFINITY, best[i] = -1;
+#pragma unroll
+                for (int jj = 0; jj < 2; ++jj) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int t = 8 * (r >> 2) + 4 * hf + (r & 3);
+                        *reinterpret_cast<float2*>(stg + t * 256 + 16 * ((l32 >> 1) ^ (t & 15)) + 8 * (l32 & 1)) =
+                            make_float2(acc[i][2 * jj][r], acc[i][2 * jj + 1][r]);
+                    }
+                    auto piece = [&](int row, int q) {
+                        return *reinterpret_cast<const float4*>(stg + row * 256 + 16 * (q ^ (row & 15)));
+                    };
+                    float* lg = a.logits + (size_t)(tb + 32 * i + rq) * HK + cr + 64 * jj + 4 * q;
+                    if (a.logits && a.K % 4 == 0) {  // whole pieces
+#pragma unroll
+                        for (int it = 0; it < 8; ++it)
+                            if (32 * i + 4 * it + rq < nt && 64 * jj + 4 * q < ncol)
+                                *reinterpret_cast<float4*>(lg + (size_t)(4 * it) * HK) = piece(4 * it + rq, q);
+                    } else if (a.logits) {
+#pragma unroll 1
+                        for (int it = 0; it < 8; ++it) {
+                            const float4 v = piece(4 * it + rq, q);
+                            const int c = 64 * jj + 4 * q;
+                            float* o = lg + (size_t)(4 * it) * HK;
+                            if (32 * i + 4 * it + rq >= nt) continue;
+                            if (c < ncol) o[0] = v.x;
+                            if (c + 1 < ncol) o[1] = v.y;
+                            if (c + 2 < ncol) o[2] = v.z;
+                            if (c + 3 < ncol) o[3] = v.w;
+                        }
+                    }
+                    // first maximal column of each head, lane = token
+                    const int left = ncol - 64 * jj;
+                    float4 x = piece(l32, 0);
+#pragma unroll 1
+                    for (int p = 0; 4 * p < min(left, 64); ++p) {
+                        const float4 y = piece(l32, (p + 1) & 15);
+                        auto take = [&](float v, bool on) {
+                            if (!on) return;
+                            if ((fresh && k == 0) || v > bv[i]) bv[i] = v, best[i] = k;
+                            if (++k == a.K) {
+                                if (hf == 0 && 32 * i + l32 < nt)
+                                    a.idx[(size_t)(tb + 32 * i + l32) * a.H + hd] = best[i];
+                                k = 0;
+                                ++hd;
+                            }
+                        };
+                        take(x.x, true);
+                        take(x.y, 4 * p + 1 < left);
+                        take(x.z, 4 * p + 2 < left);
+                        take(x.w, 4 * p + 3 < left);
+                        x = y;
+                    }
+                }
+            }
+            if (a.K > 128) {  // the head's other half comes from the neighbouring wave
+                if (wn == 1 && hf == 0)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        *reinterpret_cast<float2*>(stg + (32 * i + l32) * 8) =
+                            make_float2(bv[i], __int_as_float(best[i]));
+                __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+                barrier_no_fence();
+                if (wn == 0 && hf == 0)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float2 o =
+                            *reinterpret_cast<const float2*>(stg + C::UNIT / 4 + (32 * i + l32) * 8);
+                        if (32 * i + l32 < nt)
+                            a.idx[(size_t)(tb + 32 * i + l32) * a.H + w.h0] =
+                                o.x > bv[i] ? 128 + __float_as_int(o.y) : best[i];
+                    }
+            }
+            __builtin_amdgcn_s_waitcnt(0xc07f);
+            barrier_no_fence();
+            if (wv < 2) issue_half();
+        }
+        tc += nslot;
+        if (tc >= hi) break;
+    }
+    wait_vmcnt<0>();  // nothing lands in this LDS after the workgroup ends
+}
+
 template <int BM>
 hipError_t project_dma_launch(const ProjectArgs& a, hipStream_t st) {
     using C = RouteDma<BM>;
@@ -466,12 +978,33 @@ hipError_t project_dma_launch(const ProjectArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// 256-token tiles when they still give every CU two of them
+hipError_t project_wide_launch(const ProjectArgs& a, hipStream_t st) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_project_wide),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)WideProj::LDS);
+    if (e != hipSuccess) return e;
+    // tokens of one launch: u below 2 GiB (byte offsets leave the top bit free)
+    const long long fit = ((1LL << 31) / (2LL * a.Dm) - 256) / 256 * 256;
+    for (long long t0 = 0; t0 < a.T; t0 += fit) {
+        ProjectArgs p = a;
+        p.T = (int)(a.T - t0 < fit ? a.T - t0 : fit);
+        p.u += t0 * a.Dm;
+        if (p.logits) p.logits += t0 * a.H * a.K;
+        if (p.idx) p.idx += t0 * a.H;
+        for (int j = 0; j < a.nproj; ++j) p.out[j] += t0 * 2 * a.H * a.N;
+        hipLaunchKernelGGL(k_project_wide, dim3(256), dim3(256), WideProj::LDS, st, p);
+    }
+    return hipGetLastError();
+}
+
 hipError_t project_dma(const ProjectArgs& a, hipStream_t st) {
     const int hpb = a.S ? 256 / a.K : 1;
-    const long long NT = (a.S ? (a.H + hpb - 1) / hpb : 0) + (long long)a.nproj * ((2LL * a.H * a.N + 255) / 256);
+    const long long R = 2LL * a.H * a.N, HK = a.S ? (long long)a.H * a.K : 0;
+    const long long NT = (a.S ? (a.H + hpb - 1) / hpb : 0) + (long long)a.nproj * ((R + 255) / 256);
     const long long tiles256 = (long long)((a.T + 255) / 256) * NT;
-    return tiles256 >= 512 ? project_dma_launch<256>(a, st) : project_dma_launch<128>(a, st);
+    // 256-token tiles when they still give every CU two of them
+    if (tiles256 < 512) return project_dma_launch<128>(a, st);
+    const bool wide_fits = (std::max(R, HK) + 256) * a.Dm * 2 < (1LL << 31) && R < (1 << 20) && a.Dm < (1 << 20);
+    return wide_fits && a.nproj * R >= 4 * HK ? project_wide_launch(a, st) : project_dma_launch<256>(a, st);
 }
 
 // pi[h,k,j] = argmax_i M[h,k,i,j].  A workgroup takes 64 columns of one

@@ -192,3 +192,56 @@ def test_project_layer_full_size_sampled(B, L, H, K, N, Dm):
     u = ut.reshape(B * L, Dm)[rows].to(torch.float64).numpy()[None]
     got = {k: v.reshape((B * L,) + v.shape[2:])[rows].cpu().numpy()[None] for k, v in out.items()}
     _check_project(u, St.to(torch.float64).numpy(), [w.to(torch.float64).numpy() for w in Wt], got)
+
+
+@pytest.mark.parametrize("B,L,H,K,N,Dm,kinds", [
+    (9, 3333, 31, 5, 8, 32, "Sbcd"),     # one half slice, two partial routing halves, H*2N = 496
+    (9, 3333, 31, 5, 8, 64, "Sbcd"),     # one whole slice
+    (2, 7001, 33, 2, 32, 96, "Sbcd"),    # a half tail slice, a ragged last token tile
+    (1, 16385, 13, 37, 16, 160, "Sbcd"), # K % 4 != 0, one token in the last tile
+    (4, 4100, 3, 200, 256, 64, "Sbcd"),  # a head over both halves of its tile
+    (3, 11000, 9, 1, 64, 288, "bd"),     # no routing, two projections
+    (2, 16390, 5, 128, 128, 1056, "Sbcd"),
+])
+def test_project_large_tiles(B, L, H, K, N, Dm, kinds):
+    """The 256 x 256 tiles (512 of them and more): sampled rows, the first and
+    last among them, and every row of the last token tile."""
+    print("project B=%d L=%d H=%d K=%d N=%d Dm=%d %s" % (B, L, H, K, N, Dm, kinds), flush=True)
+    T = B * L
+    g = torch.Generator().manual_seed(T + Dm)
+    ut = torch.randn((B, L, Dm), generator=g).bfloat16()
+    St = (torch.randn((H, K, Dm), generator=g) / Dm ** 0.5).bfloat16() if "S" in kinds else None
+    Wt = [(torch.randn((H, 2 * N, Dm), generator=g) * s / Dm ** 0.5).bfloat16() if k in kinds else None
+          for k, s in (("b", 1.0), ("c", 1.0), ("d", 2.0))]
+    out = pdssm.project(ut.to(DEV), St.to(DEV) if St is not None else None,
+                        *[w.to(DEV) if w is not None else None for w in Wt], N=N)
+    rng = np.random.default_rng(2)
+    rows = np.unique(np.concatenate([[0, 127, 128, 255, T - 1], np.arange(T - T % 256, T)[:128],
+                                     rng.choice(T, size=128, replace=False)]))
+    u = ut.reshape(T, Dm)[rows].double().numpy()[None]
+    got = {k: v.reshape((T,) + v.shape[2:])[rows].cpu().numpy()[None] for k, v in out.items()}
+    _check_project(u, St.double().numpy() if St is not None else None,
+                   [w.double().numpy() if w is not None else None for w in Wt], got)
+
+
+@pytest.mark.parametrize("T", [300, 33000])
+def test_project_generator_range(T):
+    """D where magnitude logits and phases leave the fast generator's range
+    (|m| >= 80, |p| >= 8192), in both tile sizes: the diagonal computed in 64
+    bits from the logits and phases that b's weights give for the same rows."""
+    H, N, Dm = 4, 128, 32
+    g = torch.Generator().manual_seed(T)
+    u = torch.randn((1, T, Dm), generator=g).bfloat16().to(DEV)
+    W = torch.randn((H, 2 * N, Dm), generator=g)
+    W[1, 1::8] *= 5000.0
+    W[2, 0::16] *= 60.0
+    W[3, 5] *= 1e6
+    W = W.bfloat16().to(DEV)
+    out = pdssm.project(u, None, W, W, W)
+    m, p = out["b"].real.double(), out["b"].imag.double()
+    assert (p.abs() > 1e4).any() and (m.abs() > 100).any() and (m < -100).any()
+    ref = torch.polar(torch.sigmoid(m), p)
+    # fp32: r and the sine and cosine to a few roundings, exp's relative error growing with |m|
+    tol = 4e-7 + torch.sigmoid(m) * 2.0 ** -23 * m.abs()
+    assert ((out["D"].real.double() - ref.real).abs() <= tol).all()
+    assert ((out["D"].imag.double() - ref.imag).abs() <= tol).all()
