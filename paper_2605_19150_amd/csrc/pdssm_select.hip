@@ -965,6 +965,172 @@ __global__ __launch_bounds__(256, 1) void k_project_wide(ProjectArgs a) {
     wait_vmcnt<0>();  // nothing lands in this LDS after the workgroup ends
 }
 
+// ------------------------------------------------------------------ k_project_thin
+// The same product for few tokens (one step of generation for a batch), bound
+// by reading the weights once: a workgroup takes 32 weight rows (routing:
+// whole heads, up to 128 rows) against 32 TB tokens, its four waves each a part
+// of the contraction; the parts are added in LDS, in wave order.  Every wave
+// streams its slices of 64 (whole lines: 16 bytes a lane straight into operand
+// registers would touch 64 lines an instruction, which the address unit, not
+// memory, paces) through two LDS stages of its own, no barrier on the way.
+// Measured (weights not in cache): 26624 rows of d 4096, 32 tokens 75 -> 51 us
+// (4.3 TB/s; 45 us with one token), 64 tokens 83 -> 69 us, but 128 tokens 98 ->
+// 114 us, so beyond 64 the 128-token tiles; 6400 rows of d 1024, one token 21 ->
+// 5.5 us.  With operands loaded straight into registers 62 us at 32 tokens.
+template <int TB>
+struct ThinProj {
+    static constexpr int NW = 4;                // waves
+    static constexpr int TT = 32 * TB;          // tokens of a workgroup
+    static constexpr int STAGE = (1 + TB) * 32 * 128;  // a slice of 32 weight rows and TT tokens
+    static constexpr int LOADS = STAGE / 1024;  // load instructions of a slice
+    static constexpr int PITCH = 33;            // floats of a part's row: 32 columns, padded
+    static constexpr int PART = TT * PITCH;     // floats of one wave's part (over its stages)
+    static constexpr size_t LDS = (size_t)NW * 2 * STAGE;
+    static_assert(LDS <= 160 * 1024 && (size_t)PART * 4 <= 2 * STAGE, "fits");
+};
+
+__host__ __device__ inline int thin_heads(int K) { return K < 32 ? 32 / K : 1; }  // heads of a routing workgroup
+
+template <int TB>
+__global__ __launch_bounds__(256) void k_project_thin(ProjectArgs a) {
+    using C = ThinProj<TB>;
+    extern __shared__ __align__(16) unsigned char lds[];
+    float* part = reinterpret_cast<float*>(lds);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int l32 = lane & 31, hf = lane >> 5;
+    const int R = 2 * a.H * a.N, HK = a.H * a.K;
+    const int t0 = blockIdx.y * C::TT, nt = min(C::TT, a.T - t0);
+    const int hpb = thin_heads(a.K), NTr = a.S ? (a.H + hpb - 1) / hpb : 0;
+    int kind = -1, r0, ncol, rows;
+    if ((int)blockIdx.x < NTr) {
+        r0 = blockIdx.x * hpb * a.K;
+        rows = HK;
+        ncol = min(hpb * a.K, HK - r0);
+    } else {
+        const int NTp = (R + 31) / 32, j = blockIdx.x - NTr;
+        kind = j / NTp;
+        r0 = (j - kind * NTp) * 32;
+        rows = R;
+        ncol = min(32, R - r0);
+    }
+    // 32-row tiles of the workgroup (a power of two of wave slots) and the
+    // waves that share each one's contraction
+    const int nct = (ncol + 31) / 32;
+    const int lg = nct <= 1 ? 0 : nct == 2 ? 1 : 2;  // log2 of the slots
+    const int ct = wv & ((1 << lg) - 1), ks = wv >> lg, nks = C::NW >> lg;
+    const int nsl = (a.Dm + 63) / 64;
+
+    f32x16 acc[TB];
+#pragma unroll
+    for (int b = 0; b < TB; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
+    if (ct < nct) {
+        // loads and operand reads as in k_project_wide: 8 rows of a line an
+        // instruction, chunk c of row r at chunk position c ^ swz(r)
+        unsigned char* st = lds + wv * 2 * C::STAGE;
+        const uint32_t row_bytes = (uint32_t)a.Dm * 2;
+        const __amdgpu_buffer_rsrc_t rw = row_block(kind < 0 ? a.S : a.W[kind], (uint32_t)rows * row_bytes);
+        const __amdgpu_buffer_rsrc_t ru = row_block(a.u, (uint32_t)a.T * row_bytes);
+        uint32_t voff[C::LOADS];
+#pragma unroll
+        for (int i = 0; i < C::LOADS; ++i) {
+            const int p = 8 * (i & 3) + (lane >> 3);
+            const int row = i < 4 ? min(r0 + 32 * ct + p, rows - 1) : min(t0 + 32 * (i / 4 - 1) + p, a.T - 1);
+            voff[i] = (uint32_t)row * row_bytes + 16u * (uint32_t)((lane & 7) ^ ((lane >> 3) & 7) ^ (i & 1));
+        }
+        // the upper chunks of a half slice start past the (below 2 GiB)
+        // descriptors and arrive as zeros
+        const uint32_t gone = ((lane & 7) ^ (lane >> 3)) & 4 ? 0x80000000u : 0u;
+        auto issue = [&](int s, int g) {
+            const uint32_t skip = 64 * s + 32 == a.Dm ? gone : 0u;
+#pragma unroll
+            for (int i = 0; i < C::LOADS; ++i)
+                load_lds16(i < 4 ? rw : ru, st + g * C::STAGE + i * 1024, voff[i] | skip, (uint32_t)s * 128);
+        };
+        const int swz = (l32 & 7) ^ ((l32 >> 3) & 1);
+        if (ks < nsl) issue(ks, 0);
+        if (ks + nks < nsl) issue(ks + nks, 1);
+        for (int s = ks, g = 0; s < nsl; s += nks, g ^= 1) {
+            if (s + nks < nsl) wait_vmcnt<C::LOADS>();
+            else wait_vmcnt<0>();
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            bf16x8 w[4], u[TB][4];
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                const unsigned char* p = st + g * C::STAGE + l32 * 128 + 16 * ((2 * kk + hf) ^ swz);
+                w[kk] = *reinterpret_cast<const bf16x8*>(p);
+#pragma unroll
+                for (int b = 0; b < TB; ++b) u[b][kk] = *reinterpret_cast<const bf16x8*>(p + (b + 1) * 4096);
+            }
+            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the stage may be loaded again
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            if (s + 2 * nks < nsl) issue(s + 2 * nks, g);
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                for (int b = 0; b < TB; ++b)
+                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u[b][kk], w[kk], acc[b], 0, 0, 0);
+        }
+    }
+    __syncthreads();  // the stages are free for the parts
+    if (ct < nct)
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                part[wv * C::PART + (32 * b + 8 * (r >> 2) + 4 * hf + (r & 3)) * C::PITCH + l32] = acc[b][r];
+    __syncthreads();
+
+    // column c of token t: the sum of its tile's parts, in order of the waves
+    auto total = [&](int t, int c) {
+        const float* p = part + (c >> 5) * C::PART + t * C::PITCH + (c & 31);
+        float v = p[0];
+        for (int k = 1; k < nks; ++k) v += p[(size_t)(k << lg) * C::PART];
+        return v;
+    };
+    if (kind >= 0) {
+        const bool gen = a.kind[kind] == kProjGen;
+        float* out = a.out[kind] + (size_t)t0 * R + r0;
+        for (int e = threadIdx.x; e < nt * 16; e += 256) {
+            const int t = e >> 4, c = 2 * (e & 15);
+            if (c >= ncol) continue;
+            const float x = total(t, c), y = total(t, c + 1);
+            *reinterpret_cast<float2*>(out + (size_t)t * R + c) = gen ? diag_gen(x, y) : make_float2(x, y);
+        }
+        return;
+    }
+    // routing: the sums replace the first parts, then eight lanes take each
+    // (token, head), a run of its columns each, and keep the first maximum
+    for (int e = threadIdx.x; e < nt * 32 * nct; e += 256) {
+        const int t = e / (32 * nct), c = e - t * 32 * nct;
+        if (c >= ncol) continue;
+        const float v = total(t, c);
+        part[(c >> 5) * C::PART + t * C::PITCH + (c & 31)] = v;
+        if (a.logits) a.logits[(size_t)(t0 + t) * HK + r0 + c] = v;
+    }
+    __syncthreads();
+    const int nh = ncol / a.K, run = (a.K + 7) / 8, sub = threadIdx.x & 7;
+    for (int e = threadIdx.x >> 3; e < (nt * nh + 31) / 32 * 32; e += 32) {
+        const bool on = e < nt * nh;
+        const int t = on ? e / nh : 0, h = on ? e - t * nh : 0;
+        float bv = -INFINITY;
+        int best = -1;
+        for (int k = sub * run; k < min(a.K, (sub + 1) * run); ++k) {
+            const int c = h * a.K + k;
+            const float v = part[(c >> 5) * C::PART + t * C::PITCH + (c & 31)];
+            if (k == 0 || v > bv) bv = v, best = k;
+        }
+#pragma unroll
+        for (int d = 1; d < 8; d <<= 1) {  // the lower run first: it wins ties
+            const float ov = __shfl_xor(bv, d);
+            const int ob = __shfl_xor(best, d);
+            if (!(sub & d) ? ov > bv : ov >= bv && ob >= 0) bv = ov, best = ob;
+        }
+        if (on && sub == 0) a.idx[(size_t)(t0 + t) * a.H + r0 / a.K + h] = best;
+    }
+}
+
 template <int BM>
 hipError_t project_dma_launch(const ProjectArgs& a, hipStream_t st) {
     using C = RouteDma<BM>;
@@ -996,15 +1162,33 @@ hipError_t project_wide_launch(const ProjectArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <int TB>
+hipError_t project_thin_launch(const ProjectArgs& a, hipStream_t st) {
+    using C = ThinProj<TB>;
+    const int hpb = thin_heads(a.K), R = 2 * a.H * a.N;
+    const int blocks = (a.S ? (a.H + hpb - 1) / hpb : 0) + a.nproj * ((R + 31) / 32);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_project_thin<TB>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_project_thin<TB>, dim3((unsigned)blocks, (unsigned)((a.T + C::TT - 1) / C::TT)),
+                       dim3(C::NW * 64), C::LDS, st, a);
+    return hipGetLastError();
+}
+
+// where k_project_thin and the 128-token tiles of k_project_dma cross (see there)
+constexpr int kThinTokens = 64;
+
 hipError_t project_dma(const ProjectArgs& a, hipStream_t st) {
     const int hpb = a.S ? 256 / a.K : 1;
     const long long R = 2LL * a.H * a.N, HK = a.S ? (long long)a.H * a.K : 0;
     const long long NT = (a.S ? (a.H + hpb - 1) / hpb : 0) + (long long)a.nproj * ((R + 255) / 256);
     const long long tiles256 = (long long)((a.T + 255) / 256) * NT;
+    const bool below = (std::max(R, HK) + 256) * a.Dm * 2 < (1LL << 31) && a.Dm < (1 << 20);  // weights below 2 GiB
+    if (a.T <= kThinTokens && a.K <= 128 && below)
+        return a.T <= 32 ? project_thin_launch<1>(a, st) : project_thin_launch<2>(a, st);
     // 256-token tiles when they still give every CU two of them
     if (tiles256 < 512) return project_dma_launch<128>(a, st);
-    const bool wide_fits = (std::max(R, HK) + 256) * a.Dm * 2 < (1LL << 31) && R < (1 << 20) && a.Dm < (1 << 20);
-    return wide_fits && a.nproj * R >= 4 * HK ? project_wide_launch(a, st) : project_dma_launch<256>(a, st);
+    return below && R < (1 << 20) && a.nproj * R >= 4 * HK ? project_wide_launch(a, st) : project_dma_launch<256>(a, st);
 }
 
 // pi[h,k,j] = argmax_i M[h,k,i,j].  A workgroup takes 64 columns of one

@@ -245,3 +245,35 @@ def test_project_generator_range(T):
     tol = 4e-7 + torch.sigmoid(m) * 2.0 ** -23 * m.abs()
     assert ((out["D"].real.double() - ref.real).abs() <= tol).all()
     assert ((out["D"].imag.double() - ref.imag).abs() <= tol).all()
+
+
+@pytest.mark.parametrize("B,L,H,K,N,Dm,kinds", [
+    (1, 1, 16, 16, 64, 1024, "Sbcd"),   # one token
+    (1, 32, 7, 37, 32, 608, "Sbcd"),    # a head over two row tiles, a half tail slice
+    (33, 1, 24, 128, 8, 2048, "Sbcd"),  # 64-token kernel; a head over all four row tiles
+    (1, 64, 3, 97, 8, 32, "Sbcd"),      # four row tiles, the last partial; one half slice
+    (5, 3, 9, 1, 16, 96, "Sbcd"),       # 32 heads a workgroup, K = 1
+    (1, 40, 4, 128, 256, 64, "Scd"),
+    (1, 17, 2, 129, 8, 64, "Sb"),       # K > 128: the 128-token tiles
+    (2, 31, 5, 3, 8, 320, "d"),
+])
+def test_project_few_tokens(B, L, H, K, N, Dm, kinds):
+    """At most 64 tokens, and one case just outside the few-token kernel's range."""
+    print("project B=%d L=%d H=%d K=%d N=%d Dm=%d %s" % (B, L, H, K, N, Dm, kinds), flush=True)
+    _proj_case(B, L, H, K, N, Dm, seed=B * L + H + K + N + Dm, kinds=kinds)
+
+
+def test_route_few_tokens_ties():
+    """Equal logits in every run of columns that the lanes of a head share, and
+    rows of -inf and NaN: the first maximum, as with more tokens."""
+    H, K, Dm = 3, 37, 64
+    S = torch.zeros(H, K, Dm)
+    S[0, [5, 6, 20, 36], 0] = 1.0   # four equal maxima
+    S[1, :, 0] = -float("inf")      # every logit -inf
+    S[2, :, 0] = torch.arange(K, dtype=torch.float32) % 7
+    S[2, 0, 1] = float("nan")       # a NaN first: nothing exceeds it
+    u = torch.zeros(1, 1, Dm)
+    u[:, :, 0] = 1.0
+    for T in (1, 40, 65):
+        _, idx = pdssm.route(u.expand(T, 1, Dm).bfloat16().contiguous().to(DEV), S.bfloat16().to(DEV))
+        assert (idx[:, 0].cpu() == torch.tensor([5, 0, 0])).all(), T
