@@ -196,7 +196,7 @@ size_t fused_ws_bytes(const Sizes& s, const pdssm_desc* d, int C) {
 
 // Chunked workspace: the dictionary tables (read from memory by the
 // dictionary steps), then int map, complex diag, complex term, complex
-// carry/U per chunk.
+// carry/U, sized for spans of one chunk.
 size_t chunked_ws_bytes(const Sizes& s, const pdssm_desc* d) {
     return fused_tables_bytes(s, d) + align_up(s.perChunk * 4) + 3 * align_up(s.perChunk * 8);
 }
@@ -213,7 +213,7 @@ void carve_chunked(ScanArgs& a, void* ws, const Sizes& s, const pdssm_desc* d) {
     p += align_up(s.perChunk * 8);
     a.agg_v = reinterpret_cast<float2*>(p);
     p += align_up(s.perChunk * 8);
-    a.U = reinterpret_cast<float2*>(p);  // fwd: carry when saved == NULL
+    a.U = reinterpret_cast<float2*>(p);
 }
 
 bool narrow_io(const pdssm_desc* d);
@@ -273,11 +273,36 @@ hipError_t prep_fused(pdssm::FusedArgs& f, const pdssm_desc* d, const int32_t* p
     return pdssm::launch_prep(pa, st);
 }
 
-// The chunked kernels' per-chunk buffers and dictionary tables in ws; the
+// Chunks per task of the multi-pass kernels.  A wave folds, replays or walks
+// back a span of consecutive chunks, and the serial carry pass takes one hop a
+// span: a longer span shortens that chain and the operators that are written
+// and read, but leaves fewer waves.  The span (a power of two; its at most 64
+// indices fill a wave) minimises an estimate in steps: about 2048 waves run at
+// a time, each its span's steps one after another, and a hop of the chain
+// takes about as long as a step.  Measured with spans of one chunk and these
+// (us, forward + backward): c64 B4 L4096 H16 N256 K64 (span 16) 1501 + 1767 ->
+// 697 + 1013, c64 B8 L2000 H32 N128 K128 (8) 741 + 1063 -> 622 + 961, bf16 B2
+// L8000 H4 N128 K160 (8) 426 + 445 -> 237 + 272.
+constexpr long long kSpanWaves = 2048;
+int chunk_span(const pdssm_desc* d, int tau, int C) {
+    const long long seqs = (long long)d->B * d->H;
+    int best = 1;
+    long long least = 0;
+    for (int m = 1; m * tau <= 64; m *= 2) {
+        const long long spans = (C + m - 1) / m, rounds = (seqs * spans + kSpanWaves - 1) / kSpanWaves;
+        const long long cost = rounds * m * tau + spans;
+        if (m == 1 || cost < least) best = m, least = cost;
+    }
+    return best;
+}
+
+// The chunked kernels' per-span buffers and dictionary tables in ws; the
 // tables are built there unless the caller prepared them.
 hipError_t prep_chunked(ScanArgs& a, const pdssm_desc* d, const int32_t* pi, void* ws, const Sizes& s,
                         int* status, hipStream_t st) {
     carve_chunked(a, ws, s, d);
+    a.span = chunk_span(d, a.tau, a.C);
+    a.Cs = (a.C + a.span - 1) / a.span;
     const pdssm::PrepArgs pa = carve_tables(d, pi, ws, s, status);
     a.rec = pa.rec;
     a.mtab = pa.mtab;
@@ -446,7 +471,7 @@ int pdssm_scan_fwd(const pdssm_desc* d, const int32_t* idx, const int32_t* pi,
         if (e == hipSuccess) e = pdssm::launch_fwd_fused(f, st);
     } else {
         e = prep_chunked(a, d, pi, ws, s, dev_status, st);
-        a.carry = saved ? reinterpret_cast<float2*>(saved) : a.U;
+        a.carry = reinterpret_cast<float2*>(saved);
         if (e == hipSuccess) e = pdssm::launch_fwd_chunked(a, st);
     }
     return e == hipSuccess ? PDSSM_OK : PDSSM_ERR_HIP;

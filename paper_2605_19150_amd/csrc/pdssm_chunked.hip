@@ -84,10 +84,10 @@ __global__ __launch_bounds__(256) void k_fwd_agg(ScanArgs a) {
     const int wv = wave_id(), lane = lane_id();
     const int nseq = a.B * a.H;
     const int task = blockIdx.x * kWavesPerGroup + wv;
-    if (task >= nseq * a.C) return;
-    const int seq = task / a.C, ch = task - seq * a.C;
+    if (task >= nseq * a.Cs) return;
+    const int seq = task / a.Cs, sp = task - seq * a.Cs;
     const int bb = seq / a.H, hh = seq - bb * a.H;
-    const int s0 = ch * a.tau, len = min(a.tau, a.L - s0);
+    const int s0 = sp * a.span * a.tau, len = min(a.span * a.tau, a.L - s0);
     const bool act = lane < LANES;
     float2* X = xs[wv];
     float2* Ds = dsh[wv];
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256) void k_fwd_agg(ScanArgs a) {
     uint64_t sw[SL];
     map_sorted_words<N>(pm, lane, act, mt, Ps, sts[wv], sw);
     if (act) {
-        const size_t o = ((size_t)seq * a.C + ch) * N;
+        const size_t o = ((size_t)seq * a.Cs + sp) * N;
         IV<SL> packed;
 #pragma unroll
         for (int s = 0; s < SL; ++s) packed.v[s] = (int)sw[s];
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(256) void k_fwd_carry(ScanArgs a) {
 
     CV<SL> h = cv_zero<SL>();
     if (a.h0 && act) h = ld_cv<SL>(a.h0 + (size_t)seq * N, lane);
-    const size_t o0 = (size_t)seq * a.C * N;
+    const size_t o0 = (size_t)seq * a.Cs * N;
     IV<SL> pn = {};
     CV<SL> dn = cv_zero<SL>(), vn = cv_zero<SL>();
     if (act) {
@@ -212,14 +212,14 @@ __global__ __launch_bounds__(256) void k_fwd_carry(ScanArgs a) {
         dn = ld_cv<SL>(a.agg_d + o0, lane);
         vn = ld_cv<SL>(a.agg_v + o0, lane);
     }
-    for (int ch = 0; ch < a.C; ++ch) {
-        const size_t o = o0 + (size_t)ch * N;
-        if (act) st_carry<SL>(a, o, lane, h);
+    for (int sp = 0; sp < a.Cs; ++sp) {
+        const size_t o = o0 + (size_t)sp * N;
+        if (act) st_cv<SL>(a.U + o, lane, h);
         uint64_t wc[SL];
 #pragma unroll
-        for (int s = 0; s < SL; ++s) wc[s] = (uint32_t)pn.v[s];  // sorted form of the chunk map
+        for (int s = 0; s < SL; ++s) wc[s] = (uint32_t)pn.v[s];  // sorted form of the span's map
         CV<SL> dc = dn, vc = vn;
-        if (ch + 1 < a.C && act) {
+        if (sp + 1 < a.Cs && act) {
             pn = ld_iv<SL>(a.agg_p + o + N, lane);
             dn = ld_cv<SL>(a.agg_d + o + N, lane);
             vn = ld_cv<SL>(a.agg_v + o + N, lane);
@@ -236,10 +236,10 @@ __global__ __launch_bounds__(256) void k_fwd_replay(ScanArgs a) {
     const int wv = wave_id(), lane = lane_id();
     const int nseq = a.B * a.H;
     const int task = blockIdx.x * kWavesPerGroup + wv;
-    if (task >= nseq * a.C) return;
-    const int seq = task / a.C, ch = task - seq * a.C;
+    if (task >= nseq * a.Cs) return;
+    const int seq = task / a.Cs, sp = task - seq * a.Cs;
     const int bb = seq / a.H, hh = seq - bb * a.H;
-    const int s0 = ch * a.tau, len = min(a.tau, a.L - s0);
+    const int s0 = sp * a.span * a.tau, len = min(a.span * a.tau, a.L - s0);
     const bool act = lane < LANES;
     float2* X = xs[wv];
     if (lane == 0) X[N] = make_float2(0.f, 0.f);  // zero row of the source records
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256) void k_fwd_replay(ScanArgs a) {
         kv = (unsigned)kv >= (unsigned)a.K ? 0 : kv;  // reported by k_fwd_agg
     }
     CV<SL> h = cv_zero<SL>();
-    if (act) h = ld_carry<SL>(a, ((size_t)seq * a.C + ch) * N, lane);
+    if (act) h = ld_cv<SL>(a.U + ((size_t)seq * a.Cs + sp) * N, lane);
 
     const size_t stride = (size_t)a.H * N;
     const size_t base = (((size_t)bb * a.L + s0) * a.H + hh) * N;
@@ -279,6 +279,8 @@ __global__ __launch_bounds__(256) void k_fwd_replay(ScanArgs a) {
                 cn = ld_io<SL, IO>(a.c, off, lane);
             }
         }
+        if (a.carry && t % a.tau == 0 && act)  // the state entering a chunk
+            st_carry<SL>(a, ((size_t)seq * a.C + (s0 + t) / a.tau) * N, lane, h);
         table_step<N>(X, kc, wt, h, Dt, bt, lane, act);
         float part = 0.f;
         if (act) {
@@ -300,10 +302,10 @@ __global__ __launch_bounds__(256) void k_bwd_agg(ScanArgs a) {
     const int wv = wave_id(), lane = lane_id();
     const int nseq = a.B * a.H;
     const int task = blockIdx.x * kWavesPerGroup + wv;
-    if (task >= nseq * a.C) return;
-    const int seq = task / a.C, ch = task - seq * a.C;
+    if (task >= nseq * a.Cs) return;
+    const int seq = task / a.Cs, sp = task - seq * a.Cs;
     const int bb = seq / a.H, hh = seq - bb * a.H;
-    const int s0 = ch * a.tau, len = min(a.tau, a.L - s0);
+    const int s0 = sp * a.span * a.tau, len = min(a.span * a.tau, a.L - s0);
     const bool act = lane < LANES;
     float2* G = gsh[wv];
     float2* Dm = dsh[wv];
@@ -377,7 +379,7 @@ __global__ __launch_bounds__(256) void k_bwd_agg(ScanArgs a) {
         }
     }
     if (act) {
-        const size_t o = ((size_t)seq * a.C + ch) * N;
+        const size_t o = ((size_t)seq * a.Cs + sp) * N;
         st_iv<SL>(a.agg_p + o, lane, pm);
         st_cv<SL>(a.agg_d + o, lane, dm);
         st_cv<SL>(a.agg_v + o, lane, g);
@@ -397,21 +399,21 @@ __global__ __launch_bounds__(256) void k_bwd_carry(ScanArgs a) {
 
     CV<SL> u = cv_zero<SL>();
     if (a.dhf && act) u = ld_cv<SL>(a.dhf + (size_t)seq * N, lane);
-    const size_t o0 = (size_t)seq * a.C * N;
+    const size_t o0 = (size_t)seq * a.Cs * N;
     IV<SL> pn = {};
     CV<SL> dn = cv_zero<SL>(), vn = cv_zero<SL>();
     if (act) {
-        const size_t o = o0 + (size_t)(a.C - 1) * N;
+        const size_t o = o0 + (size_t)(a.Cs - 1) * N;
         pn = ld_iv<SL>(a.agg_p + o, lane);
         dn = ld_cv<SL>(a.agg_d + o, lane);
         vn = ld_cv<SL>(a.agg_v + o, lane);
     }
-    for (int ch = a.C - 1; ch >= 0; --ch) {
-        const size_t o = o0 + (size_t)ch * N;
+    for (int sp = a.Cs - 1; sp >= 0; --sp) {
+        const size_t o = o0 + (size_t)sp * N;
         if (act) st_cv<SL>(a.U + o, lane, u);
         IV<SL> pc = pn;
         CV<SL> dc = dn, gc = vn;
-        if (ch > 0 && act) {
+        if (sp > 0 && act) {
             pn = ld_iv<SL>(a.agg_p + o - N, lane);
             dn = ld_cv<SL>(a.agg_d + o - N, lane);
             vn = ld_cv<SL>(a.agg_v + o - N, lane);
@@ -436,115 +438,117 @@ __global__ __launch_bounds__(64) void k_bwd_emit(ScanArgs a) {
     extern __shared__ float2 smem[];
     const int lane = lane_id();
     const int task = blockIdx.x;
-    const int seq = task / a.C, ch = task - seq * a.C;
+    const int seq = task / a.Cs, sp = task - seq * a.Cs;
     const int bb = seq / a.H, hh = seq - bb * a.H;
-    const int s0 = ch * a.tau, len = min(a.tau, a.L - s0);
     const bool act = lane < LANES;
     float2* Hs = smem;                           // Hs[i*N + j] = state before step s0 + i
     float2* X = smem + (size_t)(a.tau + 1) * N;  // exchange row
     if (lane == 0) X[N] = make_float2(0.f, 0.f);
 
-    int kv = 0;
-    float dyv = 0.f;
-    if (lane < len) {
-        const size_t o = ((size_t)bb * a.L + s0 + lane) * a.H + hh;
-        kv = a.idx[o];
-        kv = (unsigned)kv >= (unsigned)a.K ? 0 : kv;  // reported by k_bwd_agg
-        dyv = a.dy[o];
-    }
     const size_t stride = (size_t)a.H * N;
-    const size_t base = (((size_t)bb * a.L + s0) * a.H + hh) * N;
     const int* pih = a.pi + (size_t)hh * a.K * N;
-
-    // ---- forward recompute of the chunk's states
-    CV<SL> h = cv_zero<SL>();
-    if (act) {
-        h = ld_carry<SL>(a, ((size_t)seq * a.C + ch) * N, lane);
-        st_cv<SL>(Hs, lane, h);
-    }
-    CV<SL> Dn = cv_zero<SL>(), bn = cv_zero<SL>();
-    IV<SL> pn = {};
-    uint64_t wn[SL];
-    int kn = load_entry<N>(a, hh, readlane_i(kv, 0), lane, act, wn);
-    if (act) {
-        Dn = ld_io<SL, IO>(a.D, base, lane);
-        bn = ld_io<SL, IO>(a.b, base, lane);
-    }
-    for (int t = 0; t < len; ++t) {
-        CV<SL> Dt = Dn, bt = bn;
-        uint64_t wt[SL];
-#pragma unroll
-        for (int r = 0; r < SL; ++r) wt[r] = wn[r];
-        const int kc = kn;
-        if (t + 1 < len) {
-            kn = load_entry<N>(a, hh, readlane_i(kv, t + 1), lane, act, wn);
-            if (act) {
-                Dn = ld_io<SL, IO>(a.D, base + (t + 1) * stride, lane);
-                bn = ld_io<SL, IO>(a.b, base + (t + 1) * stride, lane);
-            }
+    CV<SL> g = cv_zero<SL>();  // what reaches the last state of the chunk at hand from later steps
+    if (act) g = ld_cv<SL>(a.U + ((size_t)seq * a.Cs + sp) * N, lane);
+    for (int ch = min((sp + 1) * a.span, a.C) - 1; ch >= sp * a.span; --ch) {
+        const int s0 = ch * a.tau, len = min(a.tau, a.L - s0);
+        int kv = 0;
+        float dyv = 0.f;
+        if (lane < len) {
+            const size_t o = ((size_t)bb * a.L + s0 + lane) * a.H + hh;
+            kv = a.idx[o];
+            kv = (unsigned)kv >= (unsigned)a.K ? 0 : kv;  // reported by k_bwd_agg
+            dyv = a.dy[o];
         }
-        table_step<N>(X, kc, wt, h, Dt, bt, lane, act);
-        if (act) st_cv<SL>(Hs + (size_t)(t + 1) * N, lane, h);
-    }
+        const size_t base = (((size_t)bb * a.L + s0) * a.H + hh) * N;
 
-    // ---- reverse walk with the true incoming gradient
-    CV<SL> g = cv_zero<SL>();
-    if (act) g = ld_cv<SL>(a.U + ((size_t)seq * a.C + ch) * N, lane);
-    CV<SL> cn = cv_zero<SL>();
-    if (act) {
-        int k = readlane_i(kv, len - 1);
-        const size_t off = base + (len - 1) * stride;
-        Dn = ld_io<SL, IO>(a.D, off, lane);
-        cn = ld_io<SL, IO>(a.c, off, lane);
-        pn = ld_iv<SL>(pih + (size_t)k * N, lane);
-    }
-    for (int t = len - 1; t >= 0; --t) {
-        CV<SL> Dt = Dn, ct = cn;
-        IV<SL> pt = pn;
-        if (t > 0 && act) {
-            int k = readlane_i(kv, t - 1);
-            const size_t off = base + (t - 1) * stride;
+        // ---- forward recompute of the chunk's states
+        CV<SL> h = cv_zero<SL>();
+        if (act) {
+            h = ld_carry<SL>(a, ((size_t)seq * a.C + ch) * N, lane);
+            st_cv<SL>(Hs, lane, h);
+        }
+        CV<SL> Dn = cv_zero<SL>(), bn = cv_zero<SL>();
+        IV<SL> pn = {};
+        uint64_t wn[SL];
+        int kn = load_entry<N>(a, hh, readlane_i(kv, 0), lane, act, wn);
+        if (act) {
+            Dn = ld_io<SL, IO>(a.D, base, lane);
+            bn = ld_io<SL, IO>(a.b, base, lane);
+        }
+        for (int t = 0; t < len; ++t) {
+            CV<SL> Dt = Dn, bt = bn;
+            uint64_t wt[SL];
+    #pragma unroll
+            for (int r = 0; r < SL; ++r) wt[r] = wn[r];
+            const int kc = kn;
+            if (t + 1 < len) {
+                kn = load_entry<N>(a, hh, readlane_i(kv, t + 1), lane, act, wn);
+                if (act) {
+                    Dn = ld_io<SL, IO>(a.D, base + (t + 1) * stride, lane);
+                    bn = ld_io<SL, IO>(a.b, base + (t + 1) * stride, lane);
+                }
+            }
+            table_step<N>(X, kc, wt, h, Dt, bt, lane, act);
+            if (act) st_cv<SL>(Hs + (size_t)(t + 1) * N, lane, h);
+        }
+
+        // ---- reverse walk with the true incoming gradient
+        CV<SL> cn = cv_zero<SL>();
+        if (act) {
+            int k = readlane_i(kv, len - 1);
+            const size_t off = base + (len - 1) * stride;
             Dn = ld_io<SL, IO>(a.D, off, lane);
             cn = ld_io<SL, IO>(a.c, off, lane);
             pn = ld_iv<SL>(pih + (size_t)k * N, lane);
         }
-        sanitize_map<N, SL>(pt);
-        const float dyt = readlane_f(dyv, t);
-        const size_t off = base + t * stride;
-        CV<SL> ht = cv_zero<SL>(), hp = cv_zero<SL>(), dct;
-        if (act) {
-            ht = ld_cv<SL>(Hs + (size_t)(t + 1) * N, lane);
-            hp = ld_cv<SL>(Hs + (size_t)t * N, lane);
-        }
-#pragma unroll
-        for (int s = 0; s < SL; ++s) {
-            g.v[s].x += dyt * ct.v[s].x;
-            g.v[s].y -= dyt * ct.v[s].y;
-            dct.v[s] = make_float2(dyt * ht.v[s].x, -dyt * ht.v[s].y);
-        }
-        wave_sync();
-        if (act) {
-            st_io<SL, IO>(a.db, off, lane, g);
-            st_io<SL, IO>(a.dc, off, lane, dct);
-            st_cv<SL>(X, lane, g);
-        }
-        wave_sync();
-        if (act) {
-            CV<SL> dDt;
-#pragma unroll
-            for (int s = 0; s < SL; ++s) {
-                float2 gp = X[pt.v[s]];
-                dDt.v[s] = cmulc(hp.v[s], gp);
-                g.v[s] = cmulc(Dt.v[s], gp);
+        for (int t = len - 1; t >= 0; --t) {
+            CV<SL> Dt = Dn, ct = cn;
+            IV<SL> pt = pn;
+            if (t > 0 && act) {
+                int k = readlane_i(kv, t - 1);
+                const size_t off = base + (t - 1) * stride;
+                Dn = ld_io<SL, IO>(a.D, off, lane);
+                cn = ld_io<SL, IO>(a.c, off, lane);
+                pn = ld_iv<SL>(pih + (size_t)k * N, lane);
             }
-            st_io<SL, IO>(a.dD, off, lane, dDt);
-        }
-        if (a.z && act) {
-            // the scaled state z_t = D_t .* h_{t-1} for the straight-through gradients
-            CV<SL> zt;
-#pragma unroll
-            for (int s = 0; s < SL; ++s) zt.v[s] = cmul(Dt.v[s], hp.v[s]);
-            st_io<SL, (IO == kIoBf16 ? kIoC64 : IO)>(a.z, off, lane, zt);  // bf16 pairs: z complex64
+            sanitize_map<N, SL>(pt);
+            const float dyt = readlane_f(dyv, t);
+            const size_t off = base + t * stride;
+            CV<SL> ht = cv_zero<SL>(), hp = cv_zero<SL>(), dct;
+            if (act) {
+                ht = ld_cv<SL>(Hs + (size_t)(t + 1) * N, lane);
+                hp = ld_cv<SL>(Hs + (size_t)t * N, lane);
+            }
+    #pragma unroll
+            for (int s = 0; s < SL; ++s) {
+                g.v[s].x += dyt * ct.v[s].x;
+                g.v[s].y -= dyt * ct.v[s].y;
+                dct.v[s] = make_float2(dyt * ht.v[s].x, -dyt * ht.v[s].y);
+            }
+            wave_sync();
+            if (act) {
+                st_io<SL, IO>(a.db, off, lane, g);
+                st_io<SL, IO>(a.dc, off, lane, dct);
+                st_cv<SL>(X, lane, g);
+            }
+            wave_sync();
+            if (act) {
+                CV<SL> dDt;
+    #pragma unroll
+                for (int s = 0; s < SL; ++s) {
+                    float2 gp = X[pt.v[s]];
+                    dDt.v[s] = cmulc(hp.v[s], gp);
+                    g.v[s] = cmulc(Dt.v[s], gp);
+                }
+                st_io<SL, IO>(a.dD, off, lane, dDt);
+            }
+            if (a.z && act) {
+                // the scaled state z_t = D_t .* h_{t-1} for the straight-through gradients
+                CV<SL> zt;
+    #pragma unroll
+                for (int s = 0; s < SL; ++s) zt.v[s] = cmul(Dt.v[s], hp.v[s]);
+                st_io<SL, (IO == kIoBf16 ? kIoC64 : IO)>(a.z, off, lane, zt);  // bf16 pairs: z complex64
+            }
         }
     }
 }
@@ -626,7 +630,7 @@ inline unsigned groups_for(long long tasks) {
 
 template <int N, int IO>
 hipError_t fwd_chunked_io(const ScanArgs& a, hipStream_t s) {
-    const long long tasks = (long long)a.B * a.H * a.C;
+    const long long tasks = (long long)a.B * a.H * a.Cs;
     auto agg = k_fwd_agg<N, IO>;
     auto replay = k_fwd_replay<N, IO>;
     hipLaunchKernelGGL(agg, dim3(groups_for(tasks)), dim3(256), 0, s, a);
@@ -637,7 +641,7 @@ hipError_t fwd_chunked_io(const ScanArgs& a, hipStream_t s) {
 
 template <int N, int IO>
 hipError_t bwd_chunked_io(const ScanArgs& a, hipStream_t s) {
-    const long long tasks = (long long)a.B * a.H * a.C;
+    const long long tasks = (long long)a.B * a.H * a.Cs;
     auto agg = k_bwd_agg<N, IO>;
     auto emit = k_bwd_emit<N, IO>;
     hipLaunchKernelGGL(agg, dim3(groups_for(tasks)), dim3(256), 0, s, a);

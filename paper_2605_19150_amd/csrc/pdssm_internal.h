@@ -9,11 +9,13 @@ namespace pdssm {
 
 // Everything a scan launch needs.  Pointers are device pointers; complex
 // tensors are float2 (re, im).  seq = b*H + h indexes a sequence; per-chunk
-// buffers are [seq][chunk][N].
+// buffers are [seq][chunk][N], per-span ones [seq][span][N].
 struct ScanArgs {
     int B, L, H, N, K;
     int tau;  // chunk length
     int C;    // ceil(L / tau)
+    int span; // multi-pass kernels: chunks per task (chunk_span), ceil(C / span) tasks a sequence
+    int Cs;
     int io;   // row format of D, b, c, dD, db, dc, z (kIoC64, kIoBf16, kIoReal: pdssm_io.h; z stays
               // complex64 with kIoBf16); the float2 pointers below are reinterpreted for the 4-byte formats
     const int* idx;
@@ -30,13 +32,13 @@ struct ScanArgs {
     float2* db;
     float2* dc;
     float2* dh0;
-    float2* carry;   // [seq][C][N] state entering each chunk (saved or workspace)
-    // per-chunk operator (pi_c, d_c) and local term (bias B_c in fwd, local
+    float2* carry;   // [seq][C][N] state entering each chunk (saved), or null (forward)
+    // per-span operator (pi_c, d_c) and local term (bias B_c in fwd, local
     // adjoint gamma_c in bwd); the forward keeps pi_c in sorted form (srt_word)
     int* agg_p;
     float2* agg_d;
     float2* agg_v;
-    float2* U;       // bwd: gradient reaching the last state of each chunk from later chunks
+    float2* U;       // per span: fwd the state entering it, bwd the gradient reaching its last state from later ones
     // per-entry dictionary tables of the prep kernel (PrepArgs), [H][K][N]
     // words and [H][K] classes: the scatter-adds of the dictionary steps
     const uint64_t* rec;

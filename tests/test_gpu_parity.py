@@ -160,6 +160,35 @@ def test_large_dictionary_chunked_path(N, K):
     check_all(inp, got, eff_chunk(inp))
 
 
+@pytest.mark.parametrize("B,L,H,N,K,chunk", [
+    (1, 3001, 1, 256, 40, 0),   # spans of 16 chunks, a short last chunk in a partial last span
+    (1, 2000, 2, 128, 130, 0),  # spans of 8
+    (2, 515, 3, 128, 130, 4),   # chunks of 4
+    (1, 2, 1, 256, 40, 4),      # a single short chunk
+])
+def test_multi_pass_spans(B, L, H, N, K, chunk):
+    """The multi-pass kernels' spans of chunks: every chunk's saved state, the
+    outputs and the gradients, with sorted-form entries, and the forward
+    without saved states."""
+    import ctypes
+    inp = make_inputs(B=B, L=L, H=H, N=N, K=K, seed=L + N, with_h0=True, with_dhf=True)
+    inp["pi"][0, 1, :9] = 3
+    inp["idx"][:, ::3, 0] = 1
+    d = pdssm.desc(B, L, H, N, K, chunk)
+    assert pdssm.uses_fused(d) == 0
+    got = run_gpu(inp, chunk=chunk)
+    check_all(inp, got, eff_chunk(inp, chunk))
+    T = to_dev(inp)
+    y = torch.empty((B, L, H), device=DEV)
+    ws = torch.empty(pdssm.workspace_size(d, pdssm.OP_FWD), dtype=torch.uint8, device=DEV)
+    P = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+    rc = pdssm.load().pdssm_scan_fwd(ctypes.byref(d), P(T["idx"]), P(T["pi"]), P(T["D"]), P(T["b"]), P(T["c"]),
+                                     P(T["h0"]), P(y), None, None, P(ws), ws.numel(), None,
+                                     ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    np.testing.assert_array_equal(y.cpu().numpy(), got["y"])
+
+
 @pytest.mark.parametrize("K,fused", [(16, 1), (32, 1), (64, 0)])
 def test_state_size_256_wave_counts(K, fused):
     """N = 256: five chunk waves (K <= 16), three (K = 32), multi-pass beyond;
