@@ -28,6 +28,8 @@
 #include "pdssm_device.h"
 #include "pdssm_internal.h"
 
+#include <type_traits>
+
 namespace pdssm {
 
 namespace {
@@ -36,18 +38,41 @@ constexpr int kWavesPerGroup = 4;
 
 // Rows of D, b, c (in) and dD, db, dc, z (out) in row format IO: off counts
 // entries; the 4-byte formats widen to (and narrow from) complex in registers
-// exactly as the single-read kernels do.
+// exactly as the single-read kernels do.  bf16 pairs stay packed until their
+// step uses them (widened as they arrive, every load would be waited for at
+// once and none would be in flight during the step before it).
 template <int SL, int IO>
-__device__ __forceinline__ CV<SL> ld_io(const float2* base, size_t off, int lane) {
+using Row = CV<SL, std::conditional_t<IO == kIoBf16, uint32_t, float2>>;
+
+template <int SL, int IO>
+__device__ __forceinline__ Row<SL, IO> ld_io(const float2* base, size_t off, int lane) {
     if constexpr (IO == kIoC64) {
         return ld_cv<SL>(base + off, lane);
     } else {
         const uint32_t* p = reinterpret_cast<const uint32_t*>(base) + off + (size_t)lane * SL;
-        CV<SL> out;
+        Row<SL, IO> out;
 #pragma unroll
-        for (int s = 0; s < SL; ++s) out.v[s] = word_to_f2<IO>(p[s]);
+        for (int s = 0; s < SL; ++s) {
+            if constexpr (IO == kIoBf16) out.v[s] = p[s];
+            else out.v[s] = word_to_f2<IO>(p[s]);
+        }
         return out;
     }
+}
+template <int SL>
+__device__ __forceinline__ CV<SL> wide(const CV<SL, uint32_t>& r) {
+    CV<SL> out;
+#pragma unroll
+    for (int s = 0; s < SL; ++s) out.v[s] = bf2_to_f2(r.v[s]);
+    return out;
+}
+template <int SL>
+__device__ __forceinline__ const CV<SL>& wide(const CV<SL>& r) {
+    return r;
+}
+template <int SL, int IO>
+__device__ __forceinline__ Row<SL, IO> zero_row() {
+    return cv_zero<SL, std::conditional_t<IO == kIoBf16, uint32_t, float2>>();
 }
 template <int SL, int IO>
 __device__ __forceinline__ void st_io(float2* base, size_t off, int lane, const CV<SL>& v) {
@@ -115,7 +140,7 @@ __global__ __launch_bounds__(256) void k_fwd_agg(ScanArgs a) {
     const size_t base = (((size_t)bb * a.L + s0) * a.H + hh) * N;
     const int* pih = a.pi + (size_t)hh * a.K * N;
 
-    CV<SL> Dn = cv_zero<SL>(), bn = cv_zero<SL>();
+    Row<SL, IO> Dn = zero_row<SL, IO>(), bn = zero_row<SL, IO>();
     IV<SL> pn = {};
     uint64_t wn[SL];
     int cn = load_entry<N>(a, hh, readlane_i(kv, 0), lane, act, wn);
@@ -126,7 +151,7 @@ __global__ __launch_bounds__(256) void k_fwd_agg(ScanArgs a) {
         pn = ld_iv<SL>(pih + (size_t)k * N, lane);
     }
     for (int t = 0; t < len; ++t) {
-        CV<SL> Dt = Dn, bt = bn;
+        const CV<SL> Dt = wide(Dn), bt = wide(bn);
         IV<SL> pt = pn;
         uint64_t wt[SL];
 #pragma unroll
@@ -256,7 +281,7 @@ __global__ __launch_bounds__(256) void k_fwd_replay(ScanArgs a) {
     const size_t base = (((size_t)bb * a.L + s0) * a.H + hh) * N;
     float* yrow = a.y + ((size_t)bb * a.L + s0) * a.H + hh;
 
-    CV<SL> Dn = cv_zero<SL>(), bn = cv_zero<SL>(), cn = cv_zero<SL>();
+    Row<SL, IO> Dn = zero_row<SL, IO>(), bn = zero_row<SL, IO>(), cn = zero_row<SL, IO>();
     uint64_t wn[SL];
     int kn = load_entry<N>(a, hh, readlane_i(kv, 0), lane, act, wn);
     if (act) {
@@ -265,7 +290,7 @@ __global__ __launch_bounds__(256) void k_fwd_replay(ScanArgs a) {
         cn = ld_io<SL, IO>(a.c, base, lane);
     }
     for (int t = 0; t < len; ++t) {
-        CV<SL> Dt = Dn, bt = bn, ct = cn;
+        const CV<SL> Dt = wide(Dn), bt = wide(bn), ct = wide(cn);
         uint64_t wt[SL];
 #pragma unroll
         for (int r = 0; r < SL; ++r) wt[r] = wn[r];
@@ -334,7 +359,7 @@ __global__ __launch_bounds__(256) void k_bwd_agg(ScanArgs a) {
         pm.v[s] = lane * SL + s;
         dm.v[s] = make_float2(1.f, 0.f);
     }
-    CV<SL> Dn = cv_zero<SL>(), cn = cv_zero<SL>();
+    Row<SL, IO> Dn = zero_row<SL, IO>(), cn = zero_row<SL, IO>();
     IV<SL> pn = {};
     if (act) {
         int k = readlane_i(kv, len - 1);
@@ -344,7 +369,7 @@ __global__ __launch_bounds__(256) void k_bwd_agg(ScanArgs a) {
         pn = ld_iv<SL>(pih + (size_t)k * N, lane);
     }
     for (int t = len - 1; t >= 0; --t) {
-        CV<SL> Dt = Dn, ct = cn;
+        const CV<SL> Dt = wide(Dn), ct = wide(cn);
         IV<SL> pt = pn;
         if (t > 0 && act) {
             int k = readlane_i(kv, t - 1);
@@ -467,7 +492,7 @@ __global__ __launch_bounds__(64) void k_bwd_emit(ScanArgs a) {
             h = ld_carry<SL>(a, ((size_t)seq * a.C + ch) * N, lane);
             st_cv<SL>(Hs, lane, h);
         }
-        CV<SL> Dn = cv_zero<SL>(), bn = cv_zero<SL>();
+        Row<SL, IO> Dn = zero_row<SL, IO>(), bn = zero_row<SL, IO>();
         IV<SL> pn = {};
         uint64_t wn[SL];
         int kn = load_entry<N>(a, hh, readlane_i(kv, 0), lane, act, wn);
@@ -476,7 +501,7 @@ __global__ __launch_bounds__(64) void k_bwd_emit(ScanArgs a) {
             bn = ld_io<SL, IO>(a.b, base, lane);
         }
         for (int t = 0; t < len; ++t) {
-            CV<SL> Dt = Dn, bt = bn;
+            const CV<SL> Dt = wide(Dn), bt = wide(bn);
             uint64_t wt[SL];
     #pragma unroll
             for (int r = 0; r < SL; ++r) wt[r] = wn[r];
@@ -493,7 +518,7 @@ __global__ __launch_bounds__(64) void k_bwd_emit(ScanArgs a) {
         }
 
         // ---- reverse walk with the true incoming gradient
-        CV<SL> cn = cv_zero<SL>();
+        Row<SL, IO> cn = zero_row<SL, IO>();
         if (act) {
             int k = readlane_i(kv, len - 1);
             const size_t off = base + (len - 1) * stride;
@@ -502,7 +527,7 @@ __global__ __launch_bounds__(64) void k_bwd_emit(ScanArgs a) {
             pn = ld_iv<SL>(pih + (size_t)k * N, lane);
         }
         for (int t = len - 1; t >= 0; --t) {
-            CV<SL> Dt = Dn, ct = cn;
+            const CV<SL> Dt = wide(Dn), ct = wide(cn);
             IV<SL> pt = pn;
             if (t > 0 && act) {
                 int k = readlane_i(kv, t - 1);

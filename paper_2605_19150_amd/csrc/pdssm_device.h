@@ -304,12 +304,9 @@ __device__ __forceinline__ void st_srow(float2* base, size_t off, int lane, cons
 __device__ __forceinline__ float2 bf2_to_f2(uint32_t w) {
     return make_float2(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
 }
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float v) {
-    const uint32_t u = __float_as_uint(v);
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-}
 __device__ __forceinline__ uint32_t f2_to_bf2(float2 v) {
-    return f32_to_bf16_bits(v.x) | (f32_to_bf16_bits(v.y) << 16);
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)v.x, (__bf16)v.y});
 }
 
 // One 4-byte entry widened to a complex value, and back (the real format
@@ -327,25 +324,25 @@ __device__ __forceinline__ uint32_t f2_to_word(float2 v) {
     else return __float_as_uint(v.x);
 }
 
-// ld_row for rows of 4-byte entries (bf16 pairs or real fp32).
-template <int SL, int AUX, int IO>
-__device__ __forceinline__ CV<SL> ld_row_w(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-    CV<SL> out;
+// ld_row for rows of bf16 pairs, left packed.
+template <int SL, int AUX>
+__device__ __forceinline__ CV<SL, uint32_t> ld_row_raw(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+    CV<SL, uint32_t> out;
     if constexpr (SL == 1) {
-        out.v[0] = word_to_f2<IO>(__builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, AUX));
+        out.v[0] = __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, AUX);
     } else if constexpr (SL == 2) {
         const uint2 q = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, AUX));
-        out.v[0] = word_to_f2<IO>(q.x);
-        out.v[1] = word_to_f2<IO>(q.y);
+        out.v[0] = q.x;
+        out.v[1] = q.y;
     } else {
 #pragma unroll
         for (int s = 0; s < SL; s += 4) {
             const uint4 q =
                 __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff + 4 * s, AUX));
-            out.v[s] = word_to_f2<IO>(q.x);
-            out.v[s + 1] = word_to_f2<IO>(q.y);
-            out.v[s + 2] = word_to_f2<IO>(q.z);
-            out.v[s + 3] = word_to_f2<IO>(q.w);
+            out.v[s] = q.x;
+            out.v[s + 1] = q.y;
+            out.v[s + 2] = q.z;
+            out.v[s + 3] = q.w;
         }
     }
     return out;

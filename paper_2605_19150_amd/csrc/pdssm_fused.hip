@@ -332,13 +332,57 @@ __device__ __forceinline__ void gather_rows(const E* V, const uint64_t* recrow, 
     }
 }
 
-// Per-chunk registers of one wave.
+// Per-chunk registers of one wave.  E: the element type, or uint32_t for bf16
+// pairs as they were loaded (RowOf).
 template <int N, int TAU, class E = float2>
 struct Chunk {
     static constexpr int SL = Lay<N>::SL;
     CV<SL, E> D[TAU], b[TAU], c[TAU];
     int kv, mv, len;
 };
+
+// What a chunk's loads leave in registers: bf16 pairs stay packed until the
+// chunk is worked on.  (Widened as they arrived, the compiler waited for one
+// row before it loaded the next: every load of a chunk a memory round trip of
+// its own at N <= 32, and in the straight-through backward at N >= 128.)
+template <int IO>
+struct RowOf {
+    using T = typename ElemOf<IO>::T;
+};
+template <>
+struct RowOf<kIoBf16> {
+    using T = uint32_t;
+};
+template <class R>
+struct ElemOfRow {
+    using T = R;
+};
+template <>
+struct ElemOfRow<uint32_t> {
+    using T = float2;
+};
+
+// The chunk's rows as elements.
+template <int N, int TAU, class E>
+__device__ __forceinline__ Chunk<N, TAU, E>& widen(Chunk<N, TAU, E>& q) {
+    return q;
+}
+template <int N, int TAU>
+__device__ __forceinline__ Chunk<N, TAU, float2> widen(Chunk<N, TAU, uint32_t>& q) {
+    Chunk<N, TAU, float2> o;
+    o.kv = q.kv;
+    o.mv = q.mv;
+    o.len = q.len;
+#pragma unroll
+    for (int t = 0; t < TAU; ++t)
+#pragma unroll
+        for (int r = 0; r < Lay<N>::SL; ++r) {
+            o.D[t].v[r] = bf2_to_f2(q.D[t].v[r]);
+            o.b[t].v[r] = bf2_to_f2(q.b[t].v[r]);
+            o.c[t].v[r] = bf2_to_f2(q.c[t].v[r]);
+        }
+    return o;
+}
 
 // The same sums reading only as many sources as the step's map needs: gk is
 // that map's max in-degree (wave-uniform), and every record byte past a
@@ -414,8 +458,8 @@ __device__ __forceinline__ void pd_step(const Smem& s, const Stage<E>& st, int l
 // AUX: cache policy of the row loads (the forward streams them, kLoadStream).
 template <int N, int TAU, bool LOAD_B, bool LOAD_C, int AUX = 0, int IO = kIoC64>
 __device__ __forceinline__ void issue_chunk(const FusedArgs& a, int bb, int hh, int ch, int lane, bool act,
-                                            Chunk<N, TAU, typename ElemOf<IO>::T>& q) {
-    using E = typename ElemOf<IO>::T;
+                                            Chunk<N, TAU, typename RowOf<IO>::T>& q) {
+    using E = typename RowOf<IO>::T;
     constexpr int SL = Lay<N>::SL;
     const int chc = min(ch, a.C - 1);  // addresses stay inside the tensors
     const int s0 = chc * TAU;
@@ -433,7 +477,7 @@ __device__ __forceinline__ void issue_chunk(const FusedArgs& a, int bb, int hh, 
     const uint32_t voff = (uint32_t)lane * SL * ESZ;
     auto ld = [&](__amdgpu_buffer_rsrc_t r, uint32_t so) {
         if constexpr (IO == kIoReal) return ld_row_r<SL, AUX>(r, voff, so);
-        else if constexpr (IO == kIoBf16) return ld_row_w<SL, AUX, IO>(r, voff, so);
+        else if constexpr (IO == kIoBf16) return ld_row_raw<SL, AUX>(r, voff, so);
         else return ld_row<SL, AUX>(r, voff, so);
     };
 #pragma unroll
@@ -674,9 +718,11 @@ __device__ __forceinline__ void publish_op(const Smem& s, int wa, int wv, int sl
 // AGG: the aggregate pass of a segment -- the wave only builds and publishes
 // the chunk operator (c is not loaded, no readout).  RUN (with AGG): the pass
 // starts from and returns to *run instead, and publishes nothing.
-template <int N, int TAU, int W, int G, bool FB, bool AGG, bool RUN = false, class E>
+template <int N, int TAU, int W, int G, bool FB, bool AGG, bool RUN = false, class R>
 __device__ __forceinline__ void fwd_chunk(const FusedArgs& a, const Smem& s, const Work& w, int lc,
-                                          Chunk<N, TAU, E>& q, bool& bad, RunState<Lay<N>::SL, E>* run = nullptr) {
+                                          Chunk<N, TAU, R>& rows, bool& bad,
+                                          RunState<Lay<N>::SL, typename ElemOfRow<R>::T>* run = nullptr) {
+    using E = typename ElemOfRow<R>::T;
     static_assert(!RUN || AGG, "a run fold is an aggregate pass");
     constexpr int SL = Lay<N>::SL, LANES = Lay<N>::LANES;
     const int wv = wave_id(), lane = lane_id();
@@ -688,6 +734,7 @@ __device__ __forceinline__ void fwd_chunk(const FusedArgs& a, const Smem& s, con
     // layout's wave count), in elements
     E* CS = reinterpret_cast<E*>(s.cs + wv * N);
     const int csb = WA * N * (int)(sizeof(float2) / sizeof(E));
+    auto&& q = widen(rows);
     finish_chunk<N, TAU>(a, s, lane, q, bad);
 
     // ---- 2. one pass: local state B, chunk operator (Pi, Delta), w_t, local readout
@@ -1064,7 +1111,8 @@ __device__ __forceinline__ void fwd_body(const FusedArgs& a, const Smem& s, cons
     constexpr int LANES = Lay<N>::LANES;
     const int wv = wave_id(), lane = lane_id();
     const bool act = lane < LANES;
-    auto issue = [&](int lc, Chunk<N, TAU, E>& q) {
+    using R = typename RowOf<IO>::T;
+    auto issue = [&](int lc, Chunk<N, TAU, R>& q) {
         issue_chunk<N, TAU, true, !AGG, kLoadStream, IO>(a, w.bb, w.hh, lc < w.nc ? w.c0 + lc : a.C, lane, act, q);
     };
     bool bad = false;
@@ -1096,7 +1144,7 @@ __device__ __forceinline__ void fwd_body(const FusedArgs& a, const Smem& s, cons
             rs.Bm.v[r] = ezero<E>();
         }
         if constexpr (PREFETCH) {
-            Chunk<N, TAU, E> qa, qb;
+            Chunk<N, TAU, R> qa, qb;
             issue(r0, qa);
             for (int lc = r0; lc < r1; lc += 2) {
                 issue(lc + 1 < r1 ? lc + 1 : w.nc, qb);
@@ -1109,7 +1157,7 @@ __device__ __forceinline__ void fwd_body(const FusedArgs& a, const Smem& s, cons
             }
         } else {
             for (int lc = r0; lc < r1; ++lc) {
-                Chunk<N, TAU, E> q;
+                Chunk<N, TAU, R> q;
                 issue(lc, q);
                 fwd_chunk<N, TAU, W, G, FB, true, true>(a, s, w, lc, q, bad, &rs);
             }
@@ -1125,7 +1173,7 @@ __device__ __forceinline__ void fwd_body(const FusedArgs& a, const Smem& s, cons
     const int WA = active_waves<W>(w);
     if (wv >= WA) return;
     if constexpr (PREFETCH) {
-        Chunk<N, TAU, E> qa, qb;
+        Chunk<N, TAU, R> qa, qb;
         issue(wv, qa);
         for (int lc = wv; lc < w.nc; lc += 2 * WA) {
             issue(lc + WA, qb);
@@ -1138,7 +1186,7 @@ __device__ __forceinline__ void fwd_body(const FusedArgs& a, const Smem& s, cons
         }
     } else {
         for (int lc = wv; lc < w.nc; lc += WA) {
-            Chunk<N, TAU, E> q;
+            Chunk<N, TAU, R> q;
             issue(lc, q);
             fwd_chunk<N, TAU, W, G, FB, AGG>(a, s, w, lc, q, bad);
         }
@@ -1213,10 +1261,10 @@ __device__ __forceinline__ void st_out(void* rows, size_t off, int lane, const C
 }
 // Per-chunk registers of the backward: the chunk's rows, the saved state
 // entering it and its dy values (lane t holds dy of step t).
-template <int N, int TAU, class E>
+template <int N, int TAU, int IO>
 struct BwdChunk {
-    Chunk<N, TAU, E> q;
-    CV<Lay<N>::SL, E> hs;
+    Chunk<N, TAU, typename RowOf<IO>::T> q;
+    CV<Lay<N>::SL, typename ElemOf<IO>::T> hs;
     float dyv;
 };
 
@@ -1225,7 +1273,7 @@ struct BwdChunk {
 // does.  The aggregate pass needs neither b nor the saved states.
 template <int N, int TAU, bool AGG, int IO>
 __device__ __forceinline__ void issue_bwd(const FusedArgs& a, const Work& w, int r, int lane, bool act,
-                                          BwdChunk<N, TAU, typename ElemOf<IO>::T>& u) {
+                                          BwdChunk<N, TAU, IO>& u) {
     using E = typename ElemOf<IO>::T;
     constexpr int SL = Lay<N>::SL;
     const int ch = r < w.nc ? w.c0 + w.nc - 1 - r : a.C;
@@ -1242,7 +1290,7 @@ __device__ __forceinline__ void issue_bwd(const FusedArgs& a, const Work& w, int
 // composed into the running aggregate passed from wave to wave.
 template <int N, int TAU, int W, int G, bool FB, bool AGG, bool STE, int IO>
 __device__ __forceinline__ void bwd_chunk(const FusedArgs& a, const Smem& s, const Work& w, int r,
-                                          BwdChunk<N, TAU, typename ElemOf<IO>::T>& u, bool& bad) {
+                                          BwdChunk<N, TAU, IO>& u, bool& bad) {
     using E = typename ElemOf<IO>::T;
     constexpr int SL = Lay<N>::SL, LANES = Lay<N>::LANES;
     const int wv = wave_id(), lane = lane_id();
@@ -1255,7 +1303,7 @@ __device__ __forceinline__ void bwd_chunk(const FusedArgs& a, const Smem& s, con
     const int s0 = ch * TAU;
     const size_t base = (((size_t)w.bb * a.L + s0) * a.H + w.hh) * N;
     const int seq = w.seq;
-    Chunk<N, TAU, E>& q = u.q;
+    auto&& q = widen(u.q);
     finish_chunk<N, TAU>(a, s, lane, q, bad);
     const float dyv = lane < q.len ? u.dyv : 0.f;
 
@@ -1413,13 +1461,12 @@ __device__ __forceinline__ void bwd_chunk(const FusedArgs& a, const Smem& s, con
 // load of its next chunk is in flight while it computes the current one.
 template <int N, int TAU, int W, int G, bool FB, bool PREFETCH, bool AGG, bool STE, int IO>
 __device__ __forceinline__ void bwd_body(const FusedArgs& a, const Smem& s, const Work& w) {
-    using E = typename ElemOf<IO>::T;
     constexpr int LANES = Lay<N>::LANES;
     const int wv = wave_id(), lane = lane_id();
     const bool act = lane < LANES;
     bool bad = false;
     if constexpr (PREFETCH) {
-        BwdChunk<N, TAU, E> ua, ub;
+        BwdChunk<N, TAU, IO> ua, ub;
         issue_bwd<N, TAU, AGG, IO>(a, w, wv, lane, act, ua);
         for (int r = wv; r < w.nc; r += 2 * W) {
             issue_bwd<N, TAU, AGG, IO>(a, w, r + W, lane, act, ub);
@@ -1432,7 +1479,7 @@ __device__ __forceinline__ void bwd_body(const FusedArgs& a, const Smem& s, cons
         }
     } else {
         for (int r = wv; r < w.nc; r += W) {
-            BwdChunk<N, TAU, E> u;
+            BwdChunk<N, TAU, IO> u;
             issue_bwd<N, TAU, AGG, IO>(a, w, r, lane, act, u);
             bwd_chunk<N, TAU, W, G, FB, AGG, STE, IO>(a, s, w, r, u, bad);
         }
@@ -1505,7 +1552,11 @@ __global__ __launch_bounds__(W * 64) void k_bwd_fused(FusedArgs a) {
     __syncthreads();
     bool fb;
     const int G = head_variant(s, a.K, fb);
-    constexpr bool PF = fused_prefetch(N, TAU);
+    // bf16 pairs (packed until used) also fit twice at N = 128 and chunks of 8:
+    // 706 -> 671 us at hybrid-lm, 1020 -> 997 us at timeseries; with z (862 ->
+    // 870 us), real rows (585 -> 670 us) and in the forward (520 -> 559 us) the
+    // second buffer costs more than it hides.
+    constexpr bool PF = fused_prefetch(N, TAU) || (IO == kIoBf16 && !STE && N == 128 && TAU == 8);
     if (fb) bwd_body<N, TAU, W, 7, true, PF, AGG, STE, IO>(a, s, w);
     else if (G == 1) bwd_body<N, TAU, W, 1, false, PF, AGG, STE, IO>(a, s, w);
     else if (G == 3) bwd_body<N, TAU, W, 3, false, PF, AGG, STE, IO>(a, s, w);
