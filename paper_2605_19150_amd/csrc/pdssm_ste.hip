@@ -249,6 +249,38 @@ __global__ __launch_bounds__(256) void k_dict_scatter(SteGradArgs a) {
 }
 
 // ------------------------------------------------------------------ outer products and scores
+// Staged score tiles (T), and g rows in registers (GR), by row format.
+// complex64 and bf16 pairs: complex tile entries.  Real rows: fp32, whose
+// scores take one multiply-add per gathered entry (the complex form's second
+// one, 0 * 0 + v, returns v unchanged, v never being -0, so both give the same
+// bits).  bf16 pairs stay the packed words they are stored as until they are
+// used: widened where they are loaded, each load would be waited for there.
+// Packed tiles (half the gathered bytes) measured slower: B8 L4096 H32 N128
+// K64, whole training step 3894 -> 4162 us, since the widening adds two VALU
+// instructions a gather.
+template <int IO>
+struct TileOf {
+    using T = float2;
+    using GR = float2;
+};
+template <>
+struct TileOf<kIoReal> {
+    using T = float;
+    using GR = float2;
+};
+template <>
+struct TileOf<kIoBf16> {
+    using T = float2;
+    using GR = uint32_t;
+};
+__device__ __forceinline__ float tile_elem(float2 x, float) { return x.x; }
+__device__ __forceinline__ float2 tile_elem(float2 x, float2) { return x; }
+__device__ __forceinline__ float2 tile_elem(uint32_t x, float2) { return bf2_to_f2(x); }
+__device__ __forceinline__ float2 g_wide(float2 x) { return x; }
+__device__ __forceinline__ float2 g_wide(uint32_t x) { return bf2_to_f2(x); }
+__device__ __forceinline__ float score_fma(float g, float z, float v) { return fmaf(g, z, v); }
+__device__ __forceinline__ float score_fma(float2 g, float2 z, float v) { return fmaf(g.x, z.x, fmaf(g.y, z.y, v)); }
+
 // An item's steps go in runs of RS steps that every wave of the workgroup
 // works on together.
 //   Outer products: a wave owns an NB x NB block of G[h,k] (NB = 64: 2 x 2
@@ -274,7 +306,8 @@ struct DictCfg {
     static constexpr int U = (N >= 256 || N == 64) ? 4 : 8;          // steps per load batch (N = 64: 4 measured 3% faster)
     static constexpr int NBAT = MY / U;                              // load batches per run (even)
     static constexpr int GP = RS + 1;                                // padded tile row (complex entries)
-    static constexpr int TILE_BYTES = 2 * N * GP * 8;
+    template <int IO>
+    static constexpr int TILE_BYTES = 2 * N * GP * (int)sizeof(typename TileOf<IO>::T);
     // the cross-wave sum after the loop aliases the tiles
     static constexpr int RED_BYTES = SPLIT > 1 ? (SPLIT - 1) * NB * NB * 4 : 0;
     static_assert(NBAT % 2 == 0 && NBAT >= 2, "runs are processed in pairs of batches");
@@ -282,10 +315,10 @@ struct DictCfg {
 
 __host__ __device__ inline int score_kp(int K) { return (K + 15) & ~15; }
 
-template <int N>
+template <int N, int IO>
 size_t ste_gemm_lds(int K, bool q) {
     using Cfg = DictCfg<N>;
-    const size_t stage = q ? (size_t)Cfg::TILE_BYTES + (size_t)N * score_kp(K) : 0;
+    const size_t stage = q ? (size_t)Cfg::template TILE_BYTES<IO> + (size_t)N * score_kp(K) : 0;
     return stage > (size_t)Cfg::RED_BYTES ? stage : (size_t)Cfg::RED_BYTES;
 }
 
@@ -297,7 +330,7 @@ size_t ste_gemm_lds(int K, bool q) {
 // Real rows (the real-valued model) widen to (x, 0).
 template <int N, int IO>
 __device__ __forceinline__ void load_step(const SteGradArgs& a, int u, int h, int i0, int j0, int lane,
-                                          float2& gv, float2& zv) {
+                                          typename TileOf<IO>::GR& gv, float2& zv) {
     constexpr int NB = DictCfg<N>::NB;
     const int r = NB == 64 ? lane : min(lane & 31, N - 1);
     const size_t row = ((size_t)u * a.H + h) * N;
@@ -307,11 +340,10 @@ __device__ __forceinline__ void load_step(const SteGradArgs& a, int u, int h, in
         gv = make_float2(gq, 0.f);
         zv = make_float2(zq, 0.f);
     } else if constexpr (IO == kIoBf16) {
-        // g = db in bf16 (re, im) pairs, widened exactly; z complex64
+        // g = db in bf16 (re, im) pairs; z complex64
         typedef float f32x2 __attribute__((ext_vector_type(2)));
-        const uint32_t gw = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(a.g) + row + i0 + r);
+        gv = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(a.g) + row + i0 + r);
         const f32x2 zq = __builtin_nontemporal_load(reinterpret_cast<const f32x2*>(a.z + row + j0 + r));
-        gv = bf2_to_f2(gw);
         zv = make_float2(zq.x, zq.y);
     } else {
         typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -347,23 +379,6 @@ __device__ __forceinline__ void mfma_step(f32x16 (&acc)[DictCfg<N>::TILES][DictC
     }
 }
 
-// Staged score tiles hold complex64 entries, or fp32 for real rows (the
-// real model), whose scores then take one multiply-add per gathered entry:
-// the complex form's second one, 0 * 0 + v, returns v unchanged (v is never
-// -0), so both give the same bits.
-template <int IO>
-struct TileOf {
-    using T = float2;
-};
-template <>
-struct TileOf<kIoReal> {
-    using T = float;
-};
-__device__ __forceinline__ float tile_elem(float2 x, float) { return x.x; }
-__device__ __forceinline__ float2 tile_elem(float2 x, float2) { return x; }
-__device__ __forceinline__ float score_fma(float g, float z, float v) { return fmaf(g, z, v); }
-__device__ __forceinline__ float score_fma(float2 g, float2 z, float v) { return fmaf(g.x, z.x, fmaf(g.y, z.y, v)); }
-
 // Real rows (NB = 64): G += g z^T needs no second contraction term, so one
 // v_mfma_f32_32x32x1f32 (two 32 x 32 blocks, K = 1) does the work of two
 // tiles.  accR[tj] holds tiles (0, tj) and (1, tj) as its blocks: lane l
@@ -395,9 +410,12 @@ __global__ __launch_bounds__(DictCfg<N>::WAVES * 64) void k_ste_gemm(SteGradArgs
     extern __shared__ __align__(16) unsigned char lds[];
     float* red = reinterpret_cast<float*>(lds);
     using TE = typename TileOf<IO>::T;
+    using GR = typename TileOf<IO>::GR;
     TE* Gt = reinterpret_cast<TE*>(lds);
     TE* Zt = Gt + N * GP;
-    uint8_t* dT = lds + Cfg::TILE_BYTES;
+    constexpr int kTiles = Cfg::template TILE_BYTES<IO>;
+    static_assert(kTiles % 16 == 0, "the 16-byte map reads stay aligned");
+    uint8_t* dT = lds + kTiles;
     const SteWs w = ste_ws(a);
     const int HK = a.H * a.K, KP = score_kp(a.K);
     const int item = blockIdx.x;
@@ -451,13 +469,13 @@ __global__ __launch_bounds__(DictCfg<N>::WAVES * 64) void k_ste_gemm(SteGradArgs
     // so every load below stays valid and unconditional)
     auto run_ids = [&](int r) { return ord[min(r * RS + lane, cnt - 1)]; };
     // batch b of run r (sidv = run_ids(r))
-    auto issue = [&](float2 (&gq)[U], float2 (&zq)[U], int sidv, int b) {
+    auto issue = [&](GR (&gq)[U], float2 (&zq)[U], int sidv, int b) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
             load_step<N, IO>(a, readlane_i(sidv, my0 + b * U + u), h, i0, j0, lane, gq[u], zq[u]);
     };
     // rows of batch b into the tiles: column t = the step's place in the run
-    auto stage = [&](const float2 (&gq)[U], const float2 (&zq)[U], int b) {
+    auto stage = [&](const GR (&gq)[U], const float2 (&zq)[U], int b) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int t = my0 + b * U + u;
@@ -472,12 +490,13 @@ __global__ __launch_bounds__(DictCfg<N>::WAVES * 64) void k_ste_gemm(SteGradArgs
             }
         }
     };
-    auto multiply = [&](const float2 (&gq)[U], const float2 (&zq)[U], int r, int b) {
+    auto multiply = [&](const GR (&gq)[U], const float2 (&zq)[U], int r, int b) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (r * RS + my0 + b * U + u < cnt) {
-                if constexpr (kRealG) mfma_step_real(accR, gq[u].x, zq[u].x);
-                else mfma_step<N>(acc, gq[u], zq[u], lane);
+                const float2 gw = g_wide(gq[u]);
+                if constexpr (kRealG) mfma_step_real(accR, gw.x, zq[u].x);
+                else mfma_step<N>(acc, gw, zq[u], lane);
             }
     };
     // scores of the run's steps, KW maps per task: lane l takes step l % RS
@@ -513,12 +532,18 @@ __global__ __launch_bounds__(DictCfg<N>::WAVES * 64) void k_ste_gemm(SteGradArgs
                     wds[0] = *reinterpret_cast<const uint32_t*>(dT + j * KP + kb);
                 }
             };
-            auto column = [&](const uint32_t (&wc)[NW4], TE zc) {
-                TE g[KW > 0 ? KW : 1];
+            auto gather = [&](const uint32_t (&wc)[NW4], TE (&g)[KWD]) {
 #pragma unroll
                 for (int u = 0; u < KW; ++u) g[u] = Gt[((wc[u >> 2] >> (8 * (u & 3))) & 0xff) * GP + tt];
+            };
+            auto add = [&](const TE (&g)[KWD], TE zc) {
 #pragma unroll
                 for (int u = 0; u < KW; ++u) v[u] = score_fma(g[u], zc, v[u]);
+            };
+            auto column = [&](const uint32_t (&wc)[NW4], TE zc) {
+                TE g[KWD];
+                gather(wc, g);
+                add(g, zc);
             };
             if constexpr (N == 128 && KW == 4) {
                 // blocks of 8 columns: their z and map bytes first, then
@@ -534,6 +559,39 @@ __global__ __launch_bounds__(DictCfg<N>::WAVES * 64) void k_ste_gemm(SteGradArgs
                     for (int jj = 0; jj < JB; ++jj) ld_col(jb + jj, wc[jj], zc[jj]);
 #pragma unroll
                     for (int jj = 0; jj < JB; ++jj) column(wc[jj], zc[jj]);
+                }
+            } else if constexpr (KW == 8 && N <= 128) {
+                // One column's gathers are in flight while the column before
+                // is added, and the map bytes come two columns ahead, ahead of
+                // the gathers in LDS order, so no column waits for a round
+                // trip of its own.  Without the barriers the compiler moves
+                // every read next to its use, two round trips a column.
+                // B8 L4096 H32 N128 K64 in bf16 pairs, whole training step:
+                // 3916 -> 3774 us with fences on memory, 3704 with these.
+                // N = 64 with 4 maps a task (B16 L2048 H16 K16) measured
+                // slower this way, 832 -> 846 us; 16 maps at N = 128 have no
+                // registers for two columns.
+                uint32_t w0[NW4], w1[NW4];
+                TE z0, z1;
+                TE g0[KWD], g1[KWD];
+                ld_col(0, w0, z0);
+                ld_col(1, w1, z1);
+                gather(w0, g0);
+#pragma unroll 1
+                for (int j = 0; j < N; j += 2) {
+                    TE zn;
+                    ld_col(min(j + 2, N - 1), w0, zn);
+                    gather(w1, g1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    add(g0, z0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    z0 = zn;
+                    ld_col(min(j + 3, N - 1), w1, zn);
+                    gather(w0, g0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    add(g1, z1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    z1 = zn;
                 }
             } else if constexpr (N < 256 && (KW >= 8 || N == 128)) {
                 uint32_t wc[NW4];
@@ -585,7 +643,8 @@ __global__ __launch_bounds__(DictCfg<N>::WAVES * 64) void k_ste_gemm(SteGradArgs
     // so those loads run during the scores).  Step ids come two runs ahead.
     const int nrun = (cnt + RS - 1) / RS;
     int sid = run_ids(0), sidn = run_ids(1);
-    float2 ga[U], za[U], gb[U], zb[U];
+    GR ga[U], gb[U];
+    float2 za[U], zb[U];
     issue(ga, za, sid, 0);
     issue(gb, zb, sid, 1);
     for (int r = 0; r < nrun; ++r) {
@@ -703,7 +762,9 @@ hipError_t gemm_launch(const SteGradArgs& a, hipStream_t st) {
     auto kern = a.io == kIoReal   ? k_ste_gemm<N, KW, DO_G, kIoReal>
                 : a.io == kIoBf16 ? k_ste_gemm<N, KW, DO_G, kIoBf16>
                                   : k_ste_gemm<N, KW, DO_G, kIoC64>;
-    const size_t lds = ste_gemm_lds<N>(a.K, KW > 0);
+    const size_t lds = a.io == kIoReal   ? ste_gemm_lds<N, kIoReal>(a.K, KW > 0)
+                       : a.io == kIoBf16 ? ste_gemm_lds<N, kIoBf16>(a.K, KW > 0)
+                                         : ste_gemm_lds<N, kIoC64>(a.K, KW > 0);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;

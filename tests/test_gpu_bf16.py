@@ -141,6 +141,25 @@ def test_bf16_io_multi_pass_large_dictionary():
     check(inp, exact, out)
 
 
+@pytest.mark.parametrize("N,K", [(8, 3), (16, 17), (32, 40), (64, 5), (64, 33), (64, 160), (128, 9), (128, 64),
+                                 (128, 130), (256, 5)])
+def test_bf16_ste_grads_sizes(N, K):
+    """bf16 rows of g at every state size and score-task width, runs
+    cut short: scores and G equal the complex64 call's on the widened pairs
+    bit for bit (widening is exact and the sums have the same order)."""
+    print("bf16 ste_grads N=%d K=%d" % (N, K), flush=True)
+    rng = np.random.default_rng(N + K)
+    B, L, H = 2, 301, 3
+    dev = lambda x: torch.from_numpy(x).to(DEV)
+    idx = dev(rng.integers(0, K, size=(B, L, H), dtype=np.int32))
+    pi = dev(rng.integers(0, N, size=(H, K, N), dtype=np.int32))
+    g, z = (dev(rng.standard_normal((B, L, H, N, 2)).astype(np.float32)) for _ in range(2))
+    g, z = g.bfloat16(), torch.view_as_complex(z)
+    q, G = pdssm.ste_grads(idx, pi, g, z)
+    qw, Gw = pdssm.ste_grads(idx, pi, torch.view_as_complex(g.float()), z)
+    assert torch.equal(q, qw) and torch.equal(G, Gw)
+
+
 @pytest.mark.parametrize("N,K,L", [(64, 16, 300), (128, 32, 200), (32, 5, 77)])
 def test_bf16_ste(N, K, L):
     """The straight-through pair with bf16 pairs: z stays complex64 and equals
