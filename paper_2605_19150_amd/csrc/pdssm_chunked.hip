@@ -503,7 +503,7 @@ __global__ __launch_bounds__(64) void k_bwd_emit(ScanArgs a) {
         for (int t = 0; t < len; ++t) {
             const CV<SL> Dt = wide(Dn), bt = wide(bn);
             uint64_t wt[SL];
-    #pragma unroll
+#pragma unroll
             for (int r = 0; r < SL; ++r) wt[r] = wn[r];
             const int kc = kn;
             if (t + 1 < len) {
@@ -544,7 +544,7 @@ __global__ __launch_bounds__(64) void k_bwd_emit(ScanArgs a) {
                 ht = ld_cv<SL>(Hs + (size_t)(t + 1) * N, lane);
                 hp = ld_cv<SL>(Hs + (size_t)t * N, lane);
             }
-    #pragma unroll
+#pragma unroll
             for (int s = 0; s < SL; ++s) {
                 g.v[s].x += dyt * ct.v[s].x;
                 g.v[s].y -= dyt * ct.v[s].y;
@@ -559,7 +559,7 @@ __global__ __launch_bounds__(64) void k_bwd_emit(ScanArgs a) {
             wave_sync();
             if (act) {
                 CV<SL> dDt;
-    #pragma unroll
+#pragma unroll
                 for (int s = 0; s < SL; ++s) {
                     float2 gp = X[pt.v[s]];
                     dDt.v[s] = cmulc(hp.v[s], gp);
@@ -570,7 +570,7 @@ __global__ __launch_bounds__(64) void k_bwd_emit(ScanArgs a) {
             if (a.z && act) {
                 // the scaled state z_t = D_t .* h_{t-1} for the straight-through gradients
                 CV<SL> zt;
-    #pragma unroll
+#pragma unroll
                 for (int s = 0; s < SL; ++s) zt.v[s] = cmul(Dt.v[s], hp.v[s]);
                 st_io<SL, (IO == kIoBf16 ? kIoC64 : IO)>(a.z, off, lane, zt);  // bf16 pairs: z complex64
             }
