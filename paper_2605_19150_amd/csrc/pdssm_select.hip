@@ -18,9 +18,9 @@
 // written out coalesced and each (token, head) takes its argmax, so the
 // logits are read back from nowhere.
 #include "pdssm_device.h"
+#include "pdssm_project_rule.h"
 #include "pdssm_select.h"
 
-#include <algorithm>
 #include <type_traits>
 
 namespace pdssm {
@@ -821,18 +821,18 @@ __global__ __launch_bounds__(256, 1) void k_project_wide(ProjectArgs a) {
             // one 8-byte store (32 lanes: 256 contiguous bytes of a row), never
             // waited for.  The descriptor ends after the block's last token and
             // a lane past the last column starts beyond it: those stores drop.
-            const int ncol = min(128, R - cr);
+            const int ncol = wide_cols(R, cr);
             const bool gen = a.kind[w.kind] == kProjGen;
             float* out = a.out[w.kind] + (size_t)tb * R + cr;
             const uint64_t ob = reinterpret_cast<uint64_t>(out);
             const __amdgpu_buffer_rsrc_t ro = row_block(
                 reinterpret_cast<void*>((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(ob >> 32)) << 32 |
                                         (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)ob)),
-                __builtin_amdgcn_readfirstlane(nt ? (uint32_t)((nt - 1) * R + ncol) * 4 : 0));
+                __builtin_amdgcn_readfirstlane(wide_block_bytes(nt, R, ncol)));
             uint32_t at[2];
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj)
-                at[jj] = 64 * jj + 2 * l32 < ncol ? (uint32_t)(4 * hf * R + 64 * jj + 2 * l32) * 4 : 0xc0000000u;
+                at[jj] = wide_pair_offset(4 * hf, 64 * jj + 2 * l32, R, ncol);
             float most = 0.f;  // largest |m| / kGenMag and |p| / kGenPhase seen
             auto emit = [&](auto f) {
                 uint32_t v0 = at[0], v1 = at[1], step = (uint32_t)R * 4;
@@ -1175,20 +1175,15 @@ hipError_t project_thin_launch(const ProjectArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// where k_project_thin and the 128-token tiles of k_project_dma cross (see there)
-constexpr int kThinTokens = 64;
-
 hipError_t project_dma(const ProjectArgs& a, hipStream_t st) {
-    const int hpb = a.S ? 256 / a.K : 1;
-    const long long R = 2LL * a.H * a.N, HK = a.S ? (long long)a.H * a.K : 0;
-    const long long NT = (a.S ? (a.H + hpb - 1) / hpb : 0) + (long long)a.nproj * ((R + 255) / 256);
-    const long long tiles256 = (long long)((a.T + 255) / 256) * NT;
-    const bool below = (std::max(R, HK) + 256) * a.Dm * 2 < (1LL << 31) && a.Dm < (1 << 20);  // weights below 2 GiB
-    if (a.T <= kThinTokens && a.K <= 128 && below)
-        return a.T <= 32 ? project_thin_launch<1>(a, st) : project_thin_launch<2>(a, st);
-    // 256-token tiles when they still give every CU two of them
-    if (tiles256 < 512) return project_dma_launch<128>(a, st);
-    return below && R < (1 << 20) && a.nproj * R >= 4 * HK ? project_wide_launch(a, st) : project_dma_launch<256>(a, st);
+    switch (project_kernel(a.T, a.Dm, a.H, a.K, a.N, a.S != nullptr, a.nproj)) {
+        case kProjectThin1: return project_thin_launch<1>(a, st);
+        case kProjectThin2: return project_thin_launch<2>(a, st);
+        case kProjectDma128: return project_dma_launch<128>(a, st);
+        case kProjectDma256: return project_dma_launch<256>(a, st);
+        case kProjectWide: break;
+    }
+    return project_wide_launch(a, st);
 }
 
 // pi[h,k,j] = argmax_i M[h,k,i,j].  A workgroup takes 64 columns of one

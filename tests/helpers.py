@@ -1,4 +1,9 @@
-"""Shared helpers for the GPU parity tests."""
+"""Shared helpers of the tests."""
+import ctypes
+import os
+import subprocess
+import tempfile
+
 import numpy as np
 
 from paper_2605_19150_amd.inputs import sub_sequence  # noqa: F401
@@ -77,3 +82,45 @@ def force_sorted_entries(inp, N):
         inp["pi"][2, 3, 12:21] = N // 2
     inp["idx"][:, ::2, 0] = 1
     inp["idx"][:, 1::3, 1 % H] = 0
+
+
+_RULE_SHIM = """
+#include "pdssm_project_rule.h"
+extern "C" {
+int kernel(long long T, long long Dm, long long H, long long K, long long N, int route, int nproj) {
+    return pdssm::project_kernel(T, Dm, H, K, N, route != 0, nproj);
+}
+int cols(int R, int cr) { return pdssm::wide_cols(R, cr); }
+uint32_t bytes(int nt, int R, int ncol) { return pdssm::wide_block_bytes(nt, R, ncol); }
+uint32_t pair(int row, int c, int R, int ncol) { return pdssm::wide_pair_offset(row, c, R, ncol); }
+}
+"""
+_rule = None
+
+
+class ProjectRule:
+    """csrc/pdssm_project_rule.h compiled for the CPU."""
+    NAMES = ("thin1", "thin2", "dma128", "dma256", "wide")
+
+    def __init__(self, lib):
+        self.wide_cols = lib.cols
+        self.wide_block_bytes, self.wide_pair_offset = lib.bytes, lib.pair
+        lib.bytes.restype = lib.pair.restype = ctypes.c_uint32
+        self._kernel = lib.kernel
+        self._kernel.argtypes = [ctypes.c_longlong] * 5 + [ctypes.c_int] * 2
+
+    def kernel(self, T, Dm, H, K, N, route=True, nproj=3):
+        return self.NAMES[self._kernel(T, Dm, H, K, N, route, nproj)]
+
+
+def project_rule():
+    global _rule
+    if _rule is None:
+        csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_19150_amd", "csrc")
+        with tempfile.TemporaryDirectory() as d:
+            src, so = os.path.join(d, "rule.cpp"), os.path.join(d, "rule.so")
+            with open(src, "w") as f:
+                f.write(_RULE_SHIM)
+            subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", csrc, src, "-o", so], check=True)
+            _rule = ProjectRule(ctypes.CDLL(so))
+    return _rule

@@ -16,7 +16,7 @@ they are not, the GPU's choice must score within the bar of the best).
 import numpy as np
 import pytest
 
-from helpers import assert_close_sum
+from helpers import assert_close_sum, project_rule
 from oracle import oracle_dict_argmax, oracle_project, oracle_route
 
 torch = pytest.importorskip("torch")
@@ -222,6 +222,29 @@ def test_project_large_tiles(B, L, H, K, N, Dm, kinds):
     got = {k: v.reshape((T,) + v.shape[2:])[rows].cpu().numpy()[None] for k, v in out.items()}
     _check_project(u, St.double().numpy() if St is not None else None,
                    [w.double().numpy() if w is not None else None for w in Wt], got)
+
+
+@pytest.mark.parametrize("T,H,K,N,Dm", [
+    (18817, 5, 7, 32, 64),     # one token in the last block; H*2N = 320: the last tile's second half is empty
+    (32513, 1, 16, 32, 32),    # the same with H*2N = 64
+    (18823, 17, 3, 8, 32),     # seven; H*2N = 272
+    (32901, 1, 12, 8, 32),     # five; H*2N = 16: five rows are shorter than a block is wide
+])
+def test_project_empty_half_tile(T, H, K, N, Dm):
+    """256 x 256 tiles whose second column half lies past the last column, with
+    few tokens in the last block: every row of it, and the outputs' last rows
+    whole."""
+    print("project T=%d H=%d K=%d N=%d Dm=%d" % (T, H, K, N, Dm), flush=True)
+    assert project_rule().kernel(T, Dm, H, K, N) == "wide"
+    assert 0 < T % 128 < 8 and 0 < 2 * H * N % 256 < 128
+    g = torch.Generator().manual_seed(T)
+    ut = torch.randn((1, T, Dm), generator=g).bfloat16()
+    St = (torch.randn((H, K, Dm), generator=g) / Dm ** 0.5).bfloat16()
+    Wt = [(torch.randn((H, 2 * N, Dm), generator=g) / Dm ** 0.5).bfloat16() for _ in range(3)]
+    out = pdssm.project(ut.to(DEV), St.to(DEV), *[w.to(DEV) for w in Wt])
+    rows = np.concatenate([[0, 127, 128], np.arange(T - T % 128 - 2, T)])
+    got = {k: v[:, rows].cpu().numpy() for k, v in out.items()}
+    _check_project(ut[:, rows].double().numpy(), St.double().numpy(), [w.double().numpy() for w in Wt], got)
 
 
 @pytest.mark.parametrize("T", [300, 33000])
