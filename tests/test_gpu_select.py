@@ -270,6 +270,40 @@ def test_project_generator_range(T):
     assert ((out["D"].imag.double() - ref.imag).abs() <= tol).all()
 
 
+def test_project_generator_neighbours():
+    """D of a token has the same bits whatever the tokens and columns beside it
+    hold (an entry beyond the fast generator's range among them) and in either
+    tile size; and it is within 2e-7 |D| of 64 bits on its logits and phases,
+    the most that 1 / (1 + expf(-m)) and sincosf reach there (2.1e-7 measured)."""
+    H, N, Dm, T = 4, 128, 32, 33000
+    rule = project_rule().kernel
+    assert rule(T, Dm, H, 1, N, route=False) == "wide" and rule(300, Dm, H, 1, N, route=False) == "dma128"
+    g = torch.Generator().manual_seed(5)
+    u = torch.randn((1, T, Dm), generator=g).bfloat16().to(DEV)
+    W = (torch.randn((H, 2 * N, Dm), generator=g) * 0.4).bfloat16().to(DEV)
+    out = pdssm.project(u, None, W, W, W)
+    m, p = out["b"].real.double(), out["b"].imag.double()
+    assert m.abs().max() < 80 and p.abs().max() < 8192
+    ref = torch.polar(torch.sigmoid(m), p)
+    assert ((out["D"].to(torch.complex128) - ref).abs() <= 2e-7 * ref.abs()).all()
+    loud = u.clone()
+    loud[0, 5::128] *= 1e6  # one token of every block
+    keep = torch.ones(T, dtype=torch.bool, device=DEV)
+    keep[5::128] = False
+    other = pdssm.project(loud, None, W, W, W)
+    assert (other["b"][0, 5].imag.abs() > 8192).any()
+    for k in "bcD":
+        assert torch.equal(other[k][:, keep], out[k][:, keep]), k
+    loud = W.clone()
+    loud[1, 6:8] *= 1e6     # one entry of head 1
+    ent = torch.ones((H, N), dtype=torch.bool, device=DEV)
+    ent[1, 3] = False
+    assert torch.equal(pdssm.project(u, None, None, None, loud)["D"][:, :, ent], out["D"][:, :, ent])
+    few = pdssm.project(u[:, :300].contiguous(), None, W, W, W)
+    for k in "bcD":
+        assert torch.equal(few[k], out[k][:, :300]), k
+
+
 @pytest.mark.parametrize("B,L,H,K,N,Dm,kinds", [
     (1, 1, 16, 16, 64, 1024, "Sbcd"),   # one token
     (1, 32, 7, 37, 32, 608, "Sbcd"),    # a head over two row tiles, a half tail slice
