@@ -347,6 +347,10 @@ int pdssm_route(int32_t T, int32_t Dm, int32_t H, int32_t K, const uint16_t* u, 
  * outputs 16-byte aligned, logits and idx 4-byte aligned; row offsets of
  * (T + 256) rows of u and (H*2N + 256) rows of W below 2^32 bytes
  * (else PDSSM_ERR_UNSUPPORTED).  Needs no workspace.
+ * Every sum runs over d in the same order in every call, and an entry of D
+ * depends on its own two values alone: a token's outputs have the same bits
+ * whatever other tokens the call holds, one of them or many (a choice made in
+ * generation is the one made in prefill).
  */
 int pdssm_project(int32_t T, int32_t Dm, int32_t H, int32_t K, int32_t N, const uint16_t* u,
                   const uint16_t* S, const uint16_t* Wb, const uint16_t* Wc, const uint16_t* Wd, float* logits,

@@ -979,68 +979,72 @@ __global__ __launch_bounds__(256, 1) void k_project_wide(ProjectArgs a) {
 
 // ------------------------------------------------------------------ k_project_thin
 // The same product for few tokens (one step of generation for a batch), bound
-// by reading the weights once: a workgroup takes 32 weight rows (routing:
-// whole heads, up to 128 rows) against 32 TB tokens, its four waves each a part
-// of the contraction; the parts are added in LDS, in wave order.  Every wave
-// streams its slices of 64 (whole lines: 16 bytes a lane straight into operand
-// registers would touch 64 lines an instruction, which the address unit, not
-// memory, paces) through two LDS stages of its own, no barrier on the way.
-// Measured (weights not in cache): 26624 rows of d 4096, 32 tokens 75 -> 51 us
-// (4.3 TB/s; 45 us with one token), 64 tokens 83 -> 69 us, but 128 tokens 98 ->
-// 114 us, so beyond 64 the 128-token tiles; 6400 rows of d 1024, one token 21 ->
-// 5.5 us.  With operands loaded straight into registers 62 us at 32 tokens.
-template <int TB>
+// by reading the weights once: a wave takes 32 weight rows against 32 TB tokens
+// over the whole contraction, in the other kernels' order, so a token's outputs
+// have the same bits in any call (a near-tie chooses the same map in generation
+// as in prefill).  A routing workgroup takes whole heads, up to 128 rows, and
+// the launch has as many waves a workgroup as that needs.  A wave streams its
+// slices of 64 (whole lines: 16 bytes a lane straight into operand registers
+// would touch 64 lines an instruction, which the address unit, not memory,
+// paces) through NS LDS stages of its own, no barrier on the way.
+// Stages: 8 KB of 32 tokens, 12 KB of 64.  With up to 512 waves (two a CU) 8
+// stages, with more 5, so that four fit a CU: fewer leave memory idle (6400
+// rows of d 1024, one token: 5.6 us with 8, 6.1 with 5, 8.1 with 3), more stop
+// the waves from running at once (769 waves of d 256: 7.5 us with 5, 9.7 with 6).
+// 64 tokens: 5, or 3 where four waves must fit.
+// Measured (weights not in cache), 128-token tiles -> these: 26624 rows of d
+// 4096, one token 85 -> 44 us (5.0 TB/s), 32 tokens 92 -> 51, 64 tokens 100 ->
+// 60; 6400 rows of d 1024 23 -> 5.6, 26 -> 7.2 and 30 -> 10.4; 800 rows of d
+// 4096, one token 70 -> 10.8, where one wave's chain of products is the time
+// (four waves sharing a contraction would take 8.8 there, but in another order).
+// With 128 tokens the 128-token tiles are faster (98 us against 114 for the
+// first shape), so they take over beyond 64.
+template <int TB, int NS_>
 struct ThinProj {
-    static constexpr int NW = 4;                // waves
+    static constexpr int NS = NS_;
     static constexpr int TT = 32 * TB;          // tokens of a workgroup
     static constexpr int STAGE = (1 + TB) * 32 * 128;  // a slice of 32 weight rows and TT tokens
     static constexpr int LOADS = STAGE / 1024;  // load instructions of a slice
-    static constexpr int PITCH = 33;            // floats of a part's row: 32 columns, padded
-    static constexpr int PART = TT * PITCH;     // floats of one wave's part (over its stages)
-    static constexpr size_t LDS = (size_t)NW * 2 * STAGE;
-    static_assert(LDS <= 160 * 1024 && (size_t)PART * 4 <= 2 * STAGE, "fits");
+    static constexpr int PITCH = 33;            // floats of a result row: 32 columns, padded
+    static constexpr int WAVE = NS * STAGE;     // bytes of a wave, its results over its stages
+    static_assert(TT * PITCH * 4 <= WAVE && (NS - 1) * LOADS < 64, "results fit; vmcnt range");
 };
 
 __host__ __device__ inline int thin_heads(int K) { return K < 32 ? 32 / K : 1; }  // heads of a routing workgroup
+// waves of a workgroup: those of a routing workgroup, a power of two
+__host__ __device__ inline int thin_waves(int K, bool route) { return !route || K <= 32 ? 1 : K <= 64 ? 2 : 4; }
 
-template <int TB>
+template <int TB, int NS>
 __global__ __launch_bounds__(256) void k_project_thin(ProjectArgs a) {
-    using C = ThinProj<TB>;
+    using C = ThinProj<TB, NS>;
     extern __shared__ __align__(16) unsigned char lds[];
-    float* part = reinterpret_cast<float*>(lds);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int l32 = lane & 31, hf = lane >> 5;
     const int R = 2 * a.H * a.N, HK = a.H * a.K;
     const int t0 = blockIdx.y * C::TT, nt = min(C::TT, a.T - t0);
     const int hpb = thin_heads(a.K), NTr = a.S ? (a.H + hpb - 1) / hpb : 0;
+    const int W = thin_waves(a.K, a.S != nullptr), lg = W >> 1;  // waves (1, 2, 4), their logarithm
+    const int cols = 32 * W;                                     // columns of a projection's workgroup
     int kind = -1, r0, ncol, rows;
     if ((int)blockIdx.x < NTr) {
         r0 = blockIdx.x * hpb * a.K;
         rows = HK;
         ncol = min(hpb * a.K, HK - r0);
     } else {
-        const int NTp = (R + 31) / 32, j = blockIdx.x - NTr;
+        const int NTp = (R + cols - 1) / cols, j = blockIdx.x - NTr;
         kind = j / NTp;
-        r0 = (j - kind * NTp) * 32;
+        r0 = (j - kind * NTp) * cols;
         rows = R;
-        ncol = min(32, R - r0);
+        ncol = min(cols, R - r0);
     }
-    // 32-row tiles of the workgroup (a power of two of wave slots) and the
-    // waves that share each one's contraction
-    const int nct = (ncol + 31) / 32;
-    const int lg = nct <= 1 ? 0 : nct == 2 ? 1 : 2;  // log2 of the slots
-    const int ct = wv & ((1 << lg) - 1), ks = wv >> lg, nks = C::NW >> lg;
-    const int nsl = (a.Dm + 63) / 64;
-
-    f32x16 acc[TB];
-#pragma unroll
-    for (int b = 0; b < TB; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
-    if (ct < nct) {
+    // column c of token t, in the stages of the wave that made it
+    auto at = [&](int t, int c) {
+        return reinterpret_cast<float*>(lds + (c >> 5) * C::WAVE) + t * C::PITCH + (c & 31);
+    };
+    if (32 * wv < ncol) {
         // loads and operand reads as in k_project_wide: 8 rows of a line an
         // instruction, chunk c of row r at chunk position c ^ swz(r)
-        unsigned char* st = lds + wv * 2 * C::STAGE;
+        unsigned char* st = lds + wv * C::WAVE;
         const uint32_t row_bytes = (uint32_t)a.Dm * 2;
         const __amdgpu_buffer_rsrc_t rw = row_block(kind < 0 ? a.S : a.W[kind], (uint32_t)rows * row_bytes);
         const __amdgpu_buffer_rsrc_t ru = row_block(a.u, (uint32_t)a.T * row_bytes);
@@ -1048,89 +1052,150 @@ __global__ __launch_bounds__(256) void k_project_thin(ProjectArgs a) {
 #pragma unroll
         for (int i = 0; i < C::LOADS; ++i) {
             const int p = 8 * (i & 3) + (lane >> 3);
-            const int row = i < 4 ? min(r0 + 32 * ct + p, rows - 1) : min(t0 + 32 * (i / 4 - 1) + p, a.T - 1);
+            const int row = i < 4 ? min(r0 + 32 * wv + p, rows - 1) : min(t0 + 32 * (i / 4 - 1) + p, a.T - 1);
             voff[i] = (uint32_t)row * row_bytes + 16u * (uint32_t)((lane & 7) ^ ((lane >> 3) & 7) ^ (i & 1));
         }
-        // the upper chunks of a half slice start past the (below 2 GiB)
-        // descriptors and arrive as zeros
-        const uint32_t gone = ((lane & 7) ^ (lane >> 3)) & 4 ? 0x80000000u : 0u;
-        auto issue = [&](int s, int g) {
-            const uint32_t skip = 64 * s + 32 == a.Dm ? gone : 0u;
+        // load instructions from .. to - 1 of slice s.  Of a half slice, the last
+        // one of a wave, the upper chunks then start past the (below 2 GiB)
+        // descriptors and arrive as zeros.
+        const int half = a.Dm % 64 ? a.Dm / 64 : -1;
+        auto issue = [&](int s, int g, int from, int to) {
+            if (s == half && from == 0) {
+#pragma unroll
+                for (int i = 0; i < C::LOADS; ++i) voff[i] |= ((lane & 7) ^ (lane >> 3)) & 4 ? 0x80000000u : 0u;
+            }
 #pragma unroll
             for (int i = 0; i < C::LOADS; ++i)
-                load_lds16(i < 4 ? rw : ru, st + g * C::STAGE + i * 1024, voff[i] | skip, (uint32_t)s * 128);
+                if (i >= from && i < to)
+                    load_lds16(i < 4 ? rw : ru, st + g * C::STAGE + i * 1024, voff[i], (uint32_t)s * 128);
         };
-        const int swz = (l32 & 7) ^ ((l32 >> 3) & 1);
-        if (ks < nsl) issue(ks, 0);
-        if (ks + nks < nsl) issue(ks + nks, 1);
-        for (int s = ks, g = 0; s < nsl; s += nks, g ^= 1) {
-            if (s + nks < nsl) wait_vmcnt<C::LOADS>();
-            else wait_vmcnt<0>();
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            bf16x8 w[4], u[TB][4];
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                const unsigned char* p = st + g * C::STAGE + l32 * 128 + 16 * ((2 * kk + hf) ^ swz);
-                w[kk] = *reinterpret_cast<const bf16x8*>(p);
-#pragma unroll
-                for (int b = 0; b < TB; ++b) u[b][kk] = *reinterpret_cast<const bf16x8*>(p + (b + 1) * 4096);
-            }
-            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the stage may be loaded again
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            if (s + 2 * nks < nsl) issue(s + 2 * nks, g);
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-                for (int b = 0; b < TB; ++b)
-                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u[b][kk], w[kk], acc[b], 0, 0, 0);
-        }
-    }
-    __syncthreads();  // the stages are free for the parts
-    if (ct < nct)
+        f32x16 acc[TB];
 #pragma unroll
         for (int b = 0; b < TB; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                part[wv * C::PART + (32 * b + 8 * (r >> 2) + 4 * hf + (r & 3)) * C::PITCH + l32] = acc[b][r];
+            for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
+        const int nsl = (a.Dm + 63) / 64;
+        const int swz = (l32 & 7) ^ ((l32 >> 3) & 1);
+        struct Frag {
+            bf16x8 w[4], u[TB][4];
+        } f[2];
+        // operands of a slice's 16-wide step kk from stage g
+        auto read = [&](Frag& f, int g, int kk) {
+            const unsigned char* p = st + g * C::STAGE + l32 * 128 + 16 * ((2 * kk + hf) ^ swz);
+            f.w[kk] = *reinterpret_cast<const bf16x8*>(p);
+#pragma unroll
+            for (int b = 0; b < TB; ++b) f.u[b][kk] = *reinterpret_cast<const bf16x8*>(p + (b + 1) * 4096);
+        };
+        auto multiply = [&](const Frag& f, int kk) {
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.u[b][kk], f.w[kk], acc[b], 0, 0, 0);
+        };
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+            if (i < nsl) issue(i, i, 0, C::LOADS);
+        if (nsl < NS) wait_vmcnt<0>();
+        else wait_vmcnt<(NS - 1) * C::LOADS>();
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) read(f[0], 0, kk);
+        // slice s is multiplied; between its products, each waiting for the one
+        // before, slice s + 1 is read and slice s + NS asked for, into the
+        // stage of slice s
+        int s = 0, g = 0;
+        auto step = [&](const Frag& cur, Frag& next) {
+            const int gn = g + 1 == NS ? 0 : g + 1;
+            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): slice s is in registers
+            wait_vmcnt<(NS - 2) * C::LOADS>();   // slice s + 1 is in LDS
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                multiply(cur, kk);
+                read(next, gn, kk);
+                issue(s + NS, g, kk * C::LOADS / 4, (kk + 1) * C::LOADS / 4);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            g = gn;
+            ++s;
+        };
+        while (s + NS + 1 < nsl) {
+            step(f[0], f[1]);
+            step(f[1], f[0]);
+        }
+        if (s + NS < nsl) {
+            step(f[0], f[1]);
+            f[0] = f[1];
+        }
+        // the last slices, all asked for
+        const int rem = nsl - s;
+        auto tail = [&](auto i_, auto&& self) {
+            constexpr int i = decltype(i_)::value;
+            if constexpr (i + 1 < NS)
+                if (i + 1 < rem) {
+                    g = g + 1 == NS ? 0 : g + 1;
+                    wait_vmcnt<(NS - 2 - i) * C::LOADS>();
+                    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+#pragma unroll
+                    for (int kk = 0; kk < 4; ++kk) read(f[(i + 1) & 1], g, kk);
+                }
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) multiply(f[i & 1], kk);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (i + 1 < NS)
+                if (i + 1 < rem) self(std::integral_constant<int, i + 1>{}, self);
+        };
+        tail(std::integral_constant<int, 0>{}, tail);
+        // every load has arrived and every stage has been read: the results may go there
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) *at(32 * b + 8 * (r >> 2) + 4 * hf + (r & 3), 32 * wv + l32) = acc[b][r];
+    }
     __syncthreads();
 
-    // column c of token t: the sum of its tile's parts, in order of the waves
-    auto total = [&](int t, int c) {
-        const float* p = part + (c >> 5) * C::PART + t * C::PITCH + (c & 31);
-        float v = p[0];
-        for (int k = 1; k < nks; ++k) v += p[(size_t)(k << lg) * C::PART];
-        return v;
-    };
+    const int threads = 64 * W;
     if (kind >= 0) {
         const bool gen = a.kind[kind] == kProjGen;
         float* out = a.out[kind] + (size_t)t0 * R + r0;
-        for (int e = threadIdx.x; e < nt * 16; e += 256) {
-            const int t = e >> 4, c = 2 * (e & 15);
+        for (int e = threadIdx.x; e < nt * cols / 2; e += threads) {
+            const int t = e >> lg >> 4, c = 2 * e & (cols - 1);
             if (c >= ncol) continue;
-            const float x = total(t, c), y = total(t, c + 1);
+            const float x = *at(t, c), y = *at(t, c + 1);
             *reinterpret_cast<float2*>(out + (size_t)t * R + c) = gen ? diag_gen(x, y) : make_float2(x, y);
         }
         return;
     }
-    // routing: the sums replace the first parts, then eight lanes take each
-    // (token, head), a run of its columns each, and keep the first maximum
-    for (int e = threadIdx.x; e < nt * 32 * nct; e += 256) {
-        const int t = e / (32 * nct), c = e - t * 32 * nct;
-        if (c >= ncol) continue;
-        const float v = total(t, c);
-        part[(c >> 5) * C::PART + t * C::PITCH + (c & 31)] = v;
-        if (a.logits) a.logits[(size_t)(t0 + t) * HK + r0 + c] = v;
+    if (a.logits)
+        for (int e = threadIdx.x; e < nt * cols; e += threads) {
+            const int t = e >> lg >> 5, c = e & (cols - 1);
+            if (c < ncol) a.logits[(size_t)(t0 + t) * HK + r0 + c] = *at(t, c);
+        }
+    // first maximum of each (token, head): by one lane, neighbouring lanes taking
+    // neighbouring tokens, or, of more than 64 columns (one head of 256 threads),
+    // by eight lanes, each a run of the columns (17 tokens, K = 100: 19.1 -> 16.3
+    // us a call; 64 tokens, K = 40: 7.4 by one lane, 8.9 by eight)
+    const int nh = ncol / a.K;
+    if (a.K <= 64) {
+        for (int e = threadIdx.x; e < C::TT * nh; e += threads) {
+            const int t = e % C::TT, c0 = e / C::TT * a.K;
+            if (t >= nt) continue;
+            int best = 0;
+            float bv = *at(t, c0);
+#pragma unroll 4
+            for (int k = 1; k < a.K; ++k) {
+                const float v = *at(t, c0 + k);
+                if (v > bv) bv = v, best = k;
+            }
+            a.idx[(size_t)(t0 + t) * a.H + (r0 + c0) / a.K] = best;
+        }
+        return;
     }
-    __syncthreads();
-    const int nh = ncol / a.K, run = (a.K + 7) / 8, sub = threadIdx.x & 7;
-    for (int e = threadIdx.x >> 3; e < (nt * nh + 31) / 32 * 32; e += 32) {
-        const bool on = e < nt * nh;
-        const int t = on ? e / nh : 0, h = on ? e - t * nh : 0;
+    const int run = (a.K + 7) / 8, sub = threadIdx.x & 7;
+    for (int t = threadIdx.x >> 3; t < C::TT; t += threads / 8) {
         float bv = -INFINITY;
         int best = -1;
         for (int k = sub * run; k < min(a.K, (sub + 1) * run); ++k) {
-            const int c = h * a.K + k;
-            const float v = part[(c >> 5) * C::PART + t * C::PITCH + (c & 31)];
+            const float v = *at(t, k);
             if (k == 0 || v > bv) bv = v, best = k;
         }
 #pragma unroll
@@ -1139,7 +1204,7 @@ __global__ __launch_bounds__(256) void k_project_thin(ProjectArgs a) {
             const int ob = __shfl_xor(best, d);
             if (!(sub & d) ? ov > bv : ov >= bv && ob >= 0) bv = ov, best = ob;
         }
-        if (on && sub == 0) a.idx[(size_t)(t0 + t) * a.H + r0 / a.K + h] = best;
+        if (t < nt && sub == 0) a.idx[(size_t)(t0 + t) * a.H + r0 / a.K] = best;
     }
 }
 
@@ -1174,17 +1239,25 @@ hipError_t project_wide_launch(const ProjectArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <int TB, int NS>
+hipError_t project_thin_run(const ProjectArgs& a, int blocks, int waves, hipStream_t st) {
+    using C = ThinProj<TB, NS>;
+    const int lds = waves * C::WAVE;  // at most 160 KB by the callers' choice of NS
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_project_thin<TB, NS>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_project_thin<TB, NS>), dim3((unsigned)blocks, (unsigned)((a.T + C::TT - 1) / C::TT)),
+                       dim3(64 * waves), lds, st, a);
+    return hipGetLastError();
+}
+
 template <int TB>
 hipError_t project_thin_launch(const ProjectArgs& a, hipStream_t st) {
-    using C = ThinProj<TB>;
-    const int hpb = thin_heads(a.K), R = 2 * a.H * a.N;
-    const int blocks = (a.S ? (a.H + hpb - 1) / hpb : 0) + a.nproj * ((R + 31) / 32);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_project_thin<TB>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_project_thin<TB>, dim3((unsigned)blocks, (unsigned)((a.T + C::TT - 1) / C::TT)),
-                       dim3(C::NW * 64), C::LDS, st, a);
-    return hipGetLastError();
+    const int hpb = thin_heads(a.K), W = thin_waves(a.K, a.S != nullptr), R = 2 * a.H * a.N;
+    const int blocks = (a.S ? (a.H + hpb - 1) / hpb : 0) + a.nproj * ((R + 32 * W - 1) / (32 * W));
+    if (TB == 2) return W <= 2 ? project_thin_run<2, 5>(a, blocks, W, st) : project_thin_run<2, 3>(a, blocks, W, st);
+    return W <= 2 && blocks * W <= 512 ? project_thin_run<1, 8>(a, blocks, W, st)
+                                       : project_thin_run<1, 5>(a, blocks, W, st);
 }
 
 hipError_t project_dma(const ProjectArgs& a, hipStream_t st) {

@@ -334,3 +334,27 @@ def test_route_few_tokens_ties():
     for T in (1, 40, 65):
         _, idx = pdssm.route(u.expand(T, 1, Dm).bfloat16().contiguous().to(DEV), S.bfloat16().to(DEV))
         assert (idx[:, 0].cpu() == torch.tensor([5, 0, 0])).all(), T
+
+
+@pytest.mark.parametrize("H,K,N,Dm,T,big", [
+    (16, 16, 64, 1056, 5200, "wide"),    # a half tail slice
+    (2, 100, 8, 64, 33000, "dma256"),    # a head over four waves of the few-token kernel
+    (5, 7, 32, 608, 18817, "wide"),      # half slices, partial tiles
+    (3, 50, 16, 32, 200, "dma128"),      # a contraction of half a slice
+])
+def test_project_same_bits_in_any_call(H, K, N, Dm, T, big):
+    """A token's logits, choices, b, c and D have the same bits whatever kernel
+    the call's size selects."""
+    rule = project_rule().kernel
+    g = torch.Generator().manual_seed(T + Dm)
+    u = torch.randn((1, T, Dm), generator=g).bfloat16().to(DEV)
+    S = (torch.randn((H, K, Dm), generator=g) / Dm ** 0.5).bfloat16().to(DEV)
+    W = [(torch.randn((H, 2 * N, Dm), generator=g) / Dm ** 0.5).bfloat16().to(DEV) for _ in range(3)]
+    assert rule(T, Dm, H, K, N) == big
+    ref = pdssm.project(u, S, *W)
+    for t, kernel in ((1, "thin1"), (31, "thin1"), (33, "thin2"), (64, "thin2"), (65, "dma128")):
+        assert rule(t, Dm, H, K, N) == kernel
+        for first in (0, T - t):
+            got = pdssm.project(u[:, first:first + t].contiguous(), S, *W)
+            for k in got:
+                assert torch.equal(got[k], ref[k][:, first:first + t]), (k, t, first)
