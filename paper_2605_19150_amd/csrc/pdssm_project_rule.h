@@ -30,7 +30,21 @@ constexpr ProjectKernel project_kernel(long long T, long long Dm, long long H, l
     if (T <= kThinTokens && K <= 128 && below) return T <= 32 ? kProjectThin1 : kProjectThin2;
     // 256-token tiles when they still give every CU two of them
     if (tiles256 < 512) return kProjectDma128;
-    return below && R < (1 << 20) && nproj * R >= 4 * HK ? kProjectWide : kProjectDma256;
+    // k_project_wide gains with every slice of the contraction and in the
+    // projections' epilogue; its routing tiles' epilogue, with logits, costs
+    // more than k_project_dma<256>'s, and a tile of few columns all of a tile's
+    // products.  Time of k_project_dma<256> over k_project_wide's with logits, P
+    // projection columns for each routing column:
+    //   R < 64: 0.56-0.72 at Dm 32, 0.89-0.96 at 512, 0.97-1.03 beyond;
+    //   R = 64, P 12 / 96: 0.86 / 0.87 at 32, 0.95 / 0.96 at 64, 1.02 / 1.03 at 128;
+    //   P 4-8: 0.84-0.91 at 32, 0.90-1.02 at 64, 0.97-1.13 at 128, 1.04-1.25 at
+    //     192 (of R 1024, 2048), 1.28 and more at 1024;
+    //   P 9-16: 0.85-0.98 at 32, 0.92-1.05 at 64, 0.98-1.12 at 128;
+    //   P 19 and more, R >= 128: 0.92 (a 7.03 rounds' tail), 1.02-1.36 at 32,
+    //     1.00-1.47 at 64, 1.02-1.44 at 96.
+    const long long P = HK ? nproj * R / HK : 1 << 20;
+    const bool pays = R >= 64 && (Dm >= 192 ? P >= 4 : Dm >= 128 ? P >= 8 : R >= 128 && P >= 19);
+    return below && R < (1 << 20) && nproj * R >= 4 * HK && pays ? kProjectWide : kProjectDma256;
 }
 
 // k_project_wide: a wave's block of 128 tokens x 128 columns of an output of R
@@ -42,7 +56,7 @@ constexpr int wide_cols(int R, int cr) { return R <= cr ? 0 : R - cr < 128 ? R -
 constexpr uint32_t wide_block_bytes(int nt, int R, int ncol) {
     return nt <= 0 || ncol <= 0 ? 0u : ((uint32_t)(nt - 1) * (uint32_t)R + (uint32_t)ncol) * 4u;
 }
-// Byte offset of a lane's pair at column c of token row: one past the block's
+// Byte offset of a lane's entries at column c of token row: one past the block's
 // columns lies beyond every block (at most 2^29 bytes: R < 2^20), as do rows
 // past its last token.
 constexpr uint32_t kWidePast = 0xc0000000u;

@@ -538,6 +538,14 @@ __device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t r, uint32_t vo
     __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(v.x), __float_as_uint(v.y)}, r, voff, 0, kLoadStream);
 }
 
+// row_block of wave-uniform values that were formed in vector registers.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_block(const void* base, uint32_t bytes) {
+    const uint64_t b = reinterpret_cast<uint64_t>(base);
+    return row_block(reinterpret_cast<const void*>((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32 |
+                                                   (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b)),
+                     __builtin_amdgcn_readfirstlane(bytes));
+}
+
 // A tile of the product: 256 tokens x 256 columns, the columns as two halves
 // of up to 128 (one per wave column).  Routing halves hold whole heads when
 // K <= 128; a larger head spans both halves of its tile.
@@ -836,11 +844,7 @@ __global__ __launch_bounds__(256, 1) void k_project_wide(ProjectArgs a) {
             const int ncol = wide_cols(R, cr);
             const bool gen = a.kind[w.kind] == kProjGen;
             float* out = a.out[w.kind] + (size_t)tb * R + cr;
-            const uint64_t ob = reinterpret_cast<uint64_t>(out);
-            const __amdgpu_buffer_rsrc_t ro = row_block(
-                reinterpret_cast<void*>((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(ob >> 32)) << 32 |
-                                        (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)ob)),
-                __builtin_amdgcn_readfirstlane(wide_block_bytes(nt, R, ncol)));
+            const __amdgpu_buffer_rsrc_t ro = uniform_block(out, wide_block_bytes(nt, R, ncol));
             uint32_t at[2];
 #pragma unroll
             for (int jj = 0; jj < 2; ++jj)
@@ -849,16 +853,21 @@ __global__ __launch_bounds__(256, 1) void k_project_wide(ProjectArgs a) {
             auto emit = [&](auto f) {
                 uint32_t v0 = at[0], v1 = at[1], step = (uint32_t)R * 4;
                 asm volatile("" : "+s"(step));  // row offsets formed here, not kept across the products
+                if (nt == 0 || ncol == 0) return;  // nothing of this wave's
+                auto rows = [&](auto both) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                    for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        store_pair(ro, v0, f(acc[i][0][r], acc[i][1][r]));
-                        store_pair(ro, v1, f(acc[i][2][r], acc[i][3][r]));
-                        v0 += (r & 3) == 3 ? 5 * step : step;  // token 32 i + 8 (r / 4) + r % 4 + 4 hf
-                        v1 += (r & 3) == 3 ? 5 * step : step;
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
+                        for (int r = 0; r < 16; ++r) {
+                            store_pair(ro, v0, f(acc[i][0][r], acc[i][1][r]));
+                            if constexpr (both) store_pair(ro, v1, f(acc[i][2][r], acc[i][3][r]));
+                            v0 += (r & 3) == 3 ? 5 * step : step;  // token 32 i + 8 (r / 4) + r % 4 + 4 hf
+                            v1 += (r & 3) == 3 ? 5 * step : step;
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                };
+                if (ncol > 64) rows(std::true_type{});
+                else rows(std::false_type{});
             };
             if (gen)
                 emit([&](float m, float p) {
@@ -897,6 +906,8 @@ __global__ __launch_bounds__(256, 1) void k_project_wide(ProjectArgs a) {
                 bv[i] = -INFINITY, best[i] = -1;
 #pragma unroll
                 for (int jj = 0; jj < 2; ++jj) {
+                    const int left = ncol - 64 * jj;
+                    if (left <= 0) continue;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int t = 8 * (r >> 2) + 4 * hf + (r & 3);
@@ -907,11 +918,14 @@ __global__ __launch_bounds__(256, 1) void k_project_wide(ProjectArgs a) {
                         return *reinterpret_cast<const float4*>(stg + row * 256 + 16 * (q ^ (row & 15)));
                     };
                     float* lg = a.logits + (size_t)(tb + 32 * i + rq) * HK + cr + 64 * jj + 4 * q;
-                    if (a.logits && a.K % 4 == 0) {  // whole pieces
+                    if (a.logits && a.K % 4 == 0) {  // whole pieces: eight reads, then their stores
+                        float4 v[8];
+#pragma unroll
+                        for (int it = 0; it < 8; ++it) v[it] = piece(4 * it + rq, q);
 #pragma unroll
                         for (int it = 0; it < 8; ++it)
-                            if (32 * i + 4 * it + rq < nt && 64 * jj + 4 * q < ncol)
-                                *reinterpret_cast<float4*>(lg + (size_t)(4 * it) * HK) = piece(4 * it + rq, q);
+                            if (32 * i + 4 * it + rq < nt && 4 * q < left)
+                                *reinterpret_cast<float4*>(lg + (size_t)(4 * it) * HK) = v[it];
                     } else if (a.logits) {
 #pragma unroll 1
                         for (int it = 0; it < 8; ++it) {
@@ -926,7 +940,6 @@ __global__ __launch_bounds__(256, 1) void k_project_wide(ProjectArgs a) {
                         }
                     }
                     // first maximal column of each head, lane = token
-                    const int left = ncol - 64 * jj;
                     float4 x = piece(l32, 0);
 #pragma unroll 1
                     for (int p = 0; 4 * p < min(left, 64); ++p) {

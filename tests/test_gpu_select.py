@@ -194,19 +194,23 @@ def test_project_layer_full_size_sampled(B, L, H, K, N, Dm):
     _check_project(u, St.to(torch.float64).numpy(), [w.to(torch.float64).numpy() for w in Wt], got)
 
 
-@pytest.mark.parametrize("B,L,H,K,N,Dm,kinds", [
-    (9, 3333, 31, 5, 8, 32, "Sbcd"),     # one half slice, two partial routing halves, H*2N = 496
-    (9, 3333, 31, 5, 8, 64, "Sbcd"),     # one whole slice
-    (2, 7001, 33, 2, 32, 96, "Sbcd"),    # a half tail slice, a ragged last token tile
-    (1, 16385, 13, 37, 16, 160, "Sbcd"), # K % 4 != 0, one token in the last tile
-    (4, 4100, 3, 200, 256, 64, "Sbcd"),  # a head over both halves of its tile
-    (3, 11000, 9, 1, 64, 288, "bd"),     # no routing, two projections
-    (2, 16390, 5, 128, 128, 1056, "Sbcd"),
+@pytest.mark.parametrize("B,L,H,K,N,Dm,kinds,kernel", [
+    (9, 3333, 31, 5, 8, 32, "Sbcd", "dma256"),      # two partial routing halves, H*2N = 496
+    (9, 3333, 31, 5, 8, 64, "Sbcd", "dma256"),
+    (9, 3333, 31, 5, 32, 32, "Sbcd", "wide"),       # one half slice, two partial routing halves, H*2N = 1984
+    (9, 3333, 31, 5, 32, 64, "Sbcd", "wide"),       # one whole slice
+    (2, 7001, 33, 2, 32, 96, "Sbcd", "wide"),       # a half tail slice, a ragged last token tile
+    (1, 16385, 13, 37, 16, 160, "Sbcd", "dma256"),  # K % 4 != 0, one token in the last tile
+    (4, 4100, 3, 200, 256, 64, "Sbcd", "dma256"),
+    (4, 4100, 3, 200, 256, 192, "Sbcd", "wide"),    # a head over both halves of its tile
+    (3, 11000, 9, 1, 64, 288, "bd", "wide"),        # no routing, two projections
+    (2, 16390, 5, 128, 128, 1056, "Sbcd", "wide"),
 ])
-def test_project_large_tiles(B, L, H, K, N, Dm, kinds):
-    """The 256 x 256 tiles (512 of them and more): sampled rows, the first and
-    last among them, and every row of the last token tile."""
+def test_project_large_tiles(B, L, H, K, N, Dm, kinds, kernel):
+    """256-token tiles (512 of them and more): sampled rows, the first and last
+    among them, and every row of the last token tile."""
     print("project B=%d L=%d H=%d K=%d N=%d Dm=%d %s" % (B, L, H, K, N, Dm, kinds), flush=True)
+    assert project_rule().kernel(B * L, Dm, H, K, N, "S" in kinds, len(kinds.replace("S", ""))) == kernel
     T = B * L
     g = torch.Generator().manual_seed(T + Dm)
     ut = torch.randn((B, L, Dm), generator=g).bfloat16()
@@ -226,9 +230,9 @@ def test_project_large_tiles(B, L, H, K, N, Dm, kinds):
 
 @pytest.mark.parametrize("T,H,K,N,Dm", [
     (18817, 5, 7, 32, 64),     # one token in the last block; H*2N = 320: the last tile's second half is empty
-    (32513, 1, 16, 32, 32),    # the same with H*2N = 64
-    (18823, 17, 3, 8, 32),     # seven; H*2N = 272
-    (32901, 1, 12, 8, 32),     # five; H*2N = 16: five rows are shorter than a block is wide
+    (32513, 1, 16, 32, 128),   # the same with H*2N = 64
+    (18817, 17, 3, 8, 192),    # H*2N = 272
+    (32899, 5, 3, 8, 128),     # three tokens; H*2N = 80: rows shorter than a block is wide
 ])
 def test_project_empty_half_tile(T, H, K, N, Dm):
     """256 x 256 tiles whose second column half lies past the last column, with

@@ -39,18 +39,22 @@ def test_wide_store_extent(N):
 
 
 def test_project_kernel_rule():
-    """The rule at its lines: 32, 64 tokens and K = 128; 512 tiles; projections
-    four times the routing's rows; weights of 2 GiB."""
+    """The rule at its lines: 32, 64 tokens and K = 128; 512 tiles; the shares of
+    projections and routing; few columns; weights of 2 GiB."""
     k = project_rule().kernel
     layer = dict(Dm=1024, H=16, K=16, N=64)
     assert [k(T=T, **layer) for T in (1, 32, 33, 64, 65)] == ["thin1", "thin1", "thin2", "thin2", "dma128"]
     assert k(T=1, Dm=64, H=2, K=128, N=8) == "thin1" and k(T=1, Dm=64, H=2, K=129, N=8) == "dma128"
     # 25 column tiles: 21 token tiles make 525
     assert k(T=20 * 256, **layer) == "dma128" and k(T=20 * 256 + 1, **layer) == "wide"
-    # 3 R >= 4 H K
-    big = dict(T=1 << 17, Dm=32, H=8, N=8)
-    assert k(K=12, **big) == "wide" and k(K=13, **big) == "dma256"
-    assert k(T=1 << 17, Dm=64, H=8, K=16, N=8, nproj=0) == "dma256"
+    # projection columns for each routing column, by the contraction's length
+    big = dict(T=1 << 17, H=8, N=8)  # 3 R = 384
+    for Dm, K in ((4096, 12), (192, 12), (160, 6), (128, 6), (96, 2), (32, 2)):
+        assert k(Dm=Dm, K=K, **big) == "wide" and k(Dm=Dm, K=K + 1, **big) == "dma256", (Dm, K)
+    assert k(T=1 << 17, Dm=1024, H=8, K=16, N=8, nproj=0) == "dma256"
     assert k(T=1 << 17, Dm=64, H=8, K=1, N=8, route=False, nproj=1) == "wide"
+    # few columns
+    assert [k(T=1 << 17, Dm=4096, H=H, K=1, N=8) for H in (3, 4)] == ["dma256", "wide"]
+    assert [k(T=1 << 17, Dm=96, H=H, K=1, N=8) for H in (7, 8)] == ["dma256", "wide"]
     # rows (and 256 more) of 2 GiB
     assert k(T=1, Dm=16384, H=254, K=1, N=128) == "thin1" and k(T=1, Dm=16384, H=255, K=1, N=128) == "dma256"
