@@ -201,8 +201,10 @@ def test_project_layer_full_size_sampled(B, L, H, K, N, Dm):
     (9, 3333, 31, 5, 32, 64, "Sbcd", "wide"),       # one whole slice
     (2, 7001, 33, 2, 32, 96, "Sbcd", "wide"),       # a half tail slice, a ragged last token tile
     (1, 16385, 13, 37, 16, 160, "Sbcd", "dma256"),  # K % 4 != 0, one token in the last tile
+    (1, 18817, 13, 7, 16, 160, "Sbcd", "wide"),     # K % 4 != 0, one token in the last block
     (4, 4100, 3, 200, 256, 64, "Sbcd", "dma256"),
     (4, 4100, 3, 200, 256, 192, "Sbcd", "wide"),    # a head over both halves of its tile
+    (4, 4100, 3, 130, 256, 192, "Sbcd", "wide"),    # the same, K % 4 != 0
     (3, 11000, 9, 1, 64, 288, "bd", "wide"),        # no routing, two projections
     (2, 16390, 5, 128, 128, 1056, "Sbcd", "wide"),
 ])
@@ -220,7 +222,7 @@ def test_project_large_tiles(B, L, H, K, N, Dm, kinds, kernel):
     out = pdssm.project(ut.to(DEV), St.to(DEV) if St is not None else None,
                         *[w.to(DEV) if w is not None else None for w in Wt], N=N)
     rng = np.random.default_rng(2)
-    rows = np.unique(np.concatenate([[0, 127, 128, 255, T - 1], np.arange(T - T % 256, T)[:128],
+    rows = np.unique(np.concatenate([[0, 127, 128, 255, T - 1], np.arange(T - T % 256, T),
                                      rng.choice(T, size=128, replace=False)]))
     u = ut.reshape(T, Dm)[rows].double().numpy()[None]
     got = {k: v.reshape((T,) + v.shape[2:])[rows].cpu().numpy()[None] for k, v in out.items()}
@@ -362,3 +364,36 @@ def test_project_same_bits_in_any_call(H, K, N, Dm, T, big):
             got = pdssm.project(u[:, first:first + t].contiguous(), S, *W)
             for k in got:
                 assert torch.equal(got[k], ref[k][:, first:first + t]), (k, t, first)
+
+
+@pytest.mark.parametrize("K", [5, 32, 37, 128, 200])
+def test_route_large_tiles_ties(K):
+    """Equal logits in every run of columns that lanes or waves share, rows of
+    -inf, infinities and a NaN in the 256 x 256 tiles: the first maximum."""
+    H, N, Dm, T = 6, 256, 192, 8500
+    assert project_rule().kernel(T, Dm, H, K, N) == "wide"
+    S = torch.zeros(H, K, Dm)
+    at = sorted({K // 7 + 1, K // 4, K // 3, K // 2, K - 1})  # equal maxima
+    S[0, at, 0] = 1.0
+    S[1, :, 0] = -float("inf")      # every logit -inf
+    S[2, :, 0] = torch.arange(K, dtype=torch.float32) % 7
+    S[2, 0, 1] = float("nan")       # a NaN first: nothing exceeds it
+    S[3, K - 2:, 0] = float("inf")  # the first of two infinities
+    S[4, K // 2, 1] = float("nan")  # a NaN later: it exceeds nothing
+    S[4, K - 1, 0] = 1.0
+    S[5, :, 0] = -1.0
+    S[5, K - 1, 0] = -0.5
+    u = torch.zeros(1, T, Dm)
+    u[:, :, 0] = 1.0
+    W = torch.zeros(H, 2 * N, Dm).bfloat16().to(DEV)
+    for logits in (True, False):
+        out = pdssm.project(u.bfloat16().to(DEV), S.bfloat16().to(DEV), W, W, W, logits=logits)
+        want = torch.tensor([at[0], 0, 0, K - 2, K - 1, K - 1], dtype=torch.int32)
+        assert (out["idx"][0].cpu() == want).all(), K
+        if logits:
+            lg = out["logits"][0]
+            ref = torch.stack([S[h, :, 0] for h in (0, 1, 3, 5)]).to(DEV)  # u has one entry: the scores themselves
+            ref[1] = -float("inf")
+            got = lg[:, [0, 1, 3, 5]]
+            assert torch.equal(got[:, [0, 3]], ref[[0, 3]].expand(T, 2, K))
+            assert (got[:, 1] == -float("inf")).all() and (got[:, 2, K - 2:] == float("inf")).all()
