@@ -2,6 +2,7 @@
 // layout and kernel dispatch.  Declarations and the contract are in pdssm.h.
 #include "pdssm.h"
 
+#include <algorithm>
 #include <hip/hip_runtime.h>
 
 #include <initializer_list>
@@ -276,21 +277,26 @@ hipError_t prep_fused(pdssm::FusedArgs& f, const pdssm_desc* d, const int32_t* p
 // Chunks per task of the multi-pass kernels.  A wave folds, replays or walks
 // back a span of consecutive chunks, and the serial carry pass takes one hop a
 // span: a longer span shortens that chain and the operators that are written
-// and read, but leaves fewer waves.  The span (a power of two; its at most 64
-// indices fill a wave) minimises an estimate in steps: about 2048 waves run at
-// a time, each its span's steps one after another, and a hop of the chain
-// takes about as long as a step.  Measured with spans of one chunk and these
-// (us, forward + backward): c64 B4 L4096 H16 N256 K64 (span 16) 1501 + 1767 ->
-// 697 + 1013, c64 B8 L2000 H32 N128 K128 (8) 741 + 1063 -> 622 + 961, bf16 B2
-// L8000 H4 N128 K160 (8) 426 + 445 -> 237 + 272.
-constexpr long long kSpanWaves = 2048;
+// and read, but makes every wave's own chain of steps longer.  The span (a power
+// of two; its at most 64 indices fill a wave) minimises that sum in steps of a
+// wave: a hop takes a quarter of one (0.22-0.35 measured) and a span's operator,
+// over all sequences, 1/200 each (0.0015-0.0026 to write and read, the rest in
+// what more waves cost one another).  The steps of all waves together do not
+// depend on the span.  Over 44 sizes from 1 to 512 sequences of 40 to 18000
+// steps at N = 128 and 256 in three formats, forward + backward take 1.006 of
+// the best span's time in the mean and 1.10 at most, and at most 1.07 of that
+// with spans of one chunk.  Such spans against these (us, forward + backward):
+// c64 B4 L4096 H16 N256 K64 (span 16) 1485 + 1754 -> 680 + 1025, c64 B8 L2000
+// H32 N256 K64 (16) 1815 + 2402 -> 1252 + 1929, bf16 B2 L8000 H4 N128 K160 (8)
+// 419 + 440 -> 149 + 167, real B16 L130 H16 N128 K160 (2) 41 + 53 -> 43 + 47 (4:
+// 62 + 67).
 int chunk_span(const pdssm_desc* d, int tau, int C) {
     const long long seqs = (long long)d->B * d->H;
     int best = 1;
     long long least = 0;
     for (int m = 1; m * tau <= 64; m *= 2) {
-        const long long spans = (C + m - 1) / m, rounds = (seqs * spans + kSpanWaves - 1) / kSpanWaves;
-        const long long cost = rounds * m * tau + spans;
+        const long long spans = (C + m - 1) / m, steps = std::min<long long>(m * tau, d->L);
+        const long long cost = 200 * steps + spans * (50 + seqs);
         if (m == 1 || cost < least) best = m, least = cost;
     }
     return best;

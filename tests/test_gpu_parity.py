@@ -161,9 +161,12 @@ def test_large_dictionary_chunked_path(N, K):
 
 
 @pytest.mark.parametrize("B,L,H,N,K,chunk", [
-    (1, 3001, 1, 256, 40, 0),   # spans of 16 chunks, a short last chunk in a partial last span
-    (1, 2000, 2, 128, 130, 0),  # spans of 8
+    (1, 12001, 1, 256, 40, 0),  # spans of 16 chunks, a short last chunk in a partial last span
+    (1, 3001, 1, 256, 40, 0),   # spans of 8, the same
+    (1, 2000, 2, 128, 130, 0),  # spans of 4
     (2, 515, 3, 128, 130, 4),   # chunks of 4
+    (3, 300, 20, 128, 130, 0),  # spans of 2
+    (3, 100, 20, 128, 130, 0),  # spans of one
     (1, 2, 1, 256, 40, 4),      # a single short chunk
 ])
 def test_multi_pass_spans(B, L, H, N, K, chunk):
