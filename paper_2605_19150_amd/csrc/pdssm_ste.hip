@@ -249,35 +249,27 @@ __global__ __launch_bounds__(256) void k_dict_scatter(SteGradArgs a) {
 }
 
 // ------------------------------------------------------------------ outer products and scores
-// Staged score tiles (T), and g rows in registers (GR), by row format.
-// complex64 and bf16 pairs: complex tile entries.  Real rows: fp32, whose
-// scores take one multiply-add per gathered entry (the complex form's second
-// one, 0 * 0 + v, returns v unchanged, v never being -0, so both give the same
-// bits).  bf16 pairs stay the packed words they are stored as until they are
-// used: widened where they are loaded, each load would be waited for there.
-// Packed tiles (half the gathered bytes) measured slower: B8 L4096 H32 N128
-// K64, whole training step 3894 -> 4162 us, since the widening adds two VALU
-// instructions a gather.
+// Staged score tiles by row format.  complex64 and bf16 pairs: complex entries.
+// Real rows: fp32, whose scores take one multiply-add per gathered entry (the
+// complex form's second one, 0 * 0 + v, returns v unchanged, v never being -0,
+// so both give the same bits), in half the LDS: whole training steps B8 L4096 H8
+// real K 16 / 48 / 96 at N = 32 339 / 392 / 496 -> 333 / 385 / 494 us, at 64
+// 374 / 498 / 756 -> 358 / 455 / 667, at 128 (K 16 / 64) 765 / 967 -> 704 / 888
+// (tiles of the complex entries' size -> of their own).  bf16 pairs: packed
+// tiles (half the gathered bytes) are slower, B8 L4096 H32 N128 K64, whole
+// training step 3894 -> 4162 us, since the widening adds two VALU instructions a
+// gather; g rows packed in registers until they are staged or multiplied are no
+// faster (N <= 32 and 128) or 1-2% slower (64, 256) than widened as loaded.
 template <int IO>
 struct TileOf {
     using T = float2;
-    using GR = float2;
 };
 template <>
 struct TileOf<kIoReal> {
     using T = float;
-    using GR = float2;
-};
-template <>
-struct TileOf<kIoBf16> {
-    using T = float2;
-    using GR = uint32_t;
 };
 __device__ __forceinline__ float tile_elem(float2 x, float) { return x.x; }
 __device__ __forceinline__ float2 tile_elem(float2 x, float2) { return x; }
-__device__ __forceinline__ float2 tile_elem(uint32_t x, float2) { return bf2_to_f2(x); }
-__device__ __forceinline__ float2 g_wide(float2 x) { return x; }
-__device__ __forceinline__ float2 g_wide(uint32_t x) { return bf2_to_f2(x); }
 __device__ __forceinline__ float score_fma(float g, float z, float v) { return fmaf(g, z, v); }
 __device__ __forceinline__ float score_fma(float2 g, float2 z, float v) { return fmaf(g.x, z.x, fmaf(g.y, z.y, v)); }
 
@@ -330,7 +322,7 @@ size_t ste_gemm_lds(int K, bool q) {
 // Real rows (the real-valued model) widen to (x, 0).
 template <int N, int IO>
 __device__ __forceinline__ void load_step(const SteGradArgs& a, int u, int h, int i0, int j0, int lane,
-                                          typename TileOf<IO>::GR& gv, float2& zv) {
+                                          float2& gv, float2& zv) {
     constexpr int NB = DictCfg<N>::NB;
     const int r = NB == 64 ? lane : min(lane & 31, N - 1);
     const size_t row = ((size_t)u * a.H + h) * N;
@@ -340,9 +332,9 @@ __device__ __forceinline__ void load_step(const SteGradArgs& a, int u, int h, in
         gv = make_float2(gq, 0.f);
         zv = make_float2(zq, 0.f);
     } else if constexpr (IO == kIoBf16) {
-        // g = db in bf16 (re, im) pairs; z complex64
+        // g = db in bf16 (re, im) pairs, widened exactly; z complex64
         typedef float f32x2 __attribute__((ext_vector_type(2)));
-        gv = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(a.g) + row + i0 + r);
+        gv = bf2_to_f2(__builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(a.g) + row + i0 + r));
         const f32x2 zq = __builtin_nontemporal_load(reinterpret_cast<const f32x2*>(a.z + row + j0 + r));
         zv = make_float2(zq.x, zq.y);
     } else {
@@ -410,7 +402,6 @@ __global__ __launch_bounds__(DictCfg<N>::WAVES * 64) void k_ste_gemm(SteGradArgs
     extern __shared__ __align__(16) unsigned char lds[];
     float* red = reinterpret_cast<float*>(lds);
     using TE = typename TileOf<IO>::T;
-    using GR = typename TileOf<IO>::GR;
     TE* Gt = reinterpret_cast<TE*>(lds);
     TE* Zt = Gt + N * GP;
     constexpr int kTiles = Cfg::template TILE_BYTES<IO>;
@@ -469,13 +460,13 @@ __global__ __launch_bounds__(DictCfg<N>::WAVES * 64) void k_ste_gemm(SteGradArgs
     // so every load below stays valid and unconditional)
     auto run_ids = [&](int r) { return ord[min(r * RS + lane, cnt - 1)]; };
     // batch b of run r (sidv = run_ids(r))
-    auto issue = [&](GR (&gq)[U], float2 (&zq)[U], int sidv, int b) {
+    auto issue = [&](float2 (&gq)[U], float2 (&zq)[U], int sidv, int b) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
             load_step<N, IO>(a, readlane_i(sidv, my0 + b * U + u), h, i0, j0, lane, gq[u], zq[u]);
     };
     // rows of batch b into the tiles: column t = the step's place in the run
-    auto stage = [&](const GR (&gq)[U], const float2 (&zq)[U], int b) {
+    auto stage = [&](const float2 (&gq)[U], const float2 (&zq)[U], int b) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int t = my0 + b * U + u;
@@ -490,13 +481,12 @@ __global__ __launch_bounds__(DictCfg<N>::WAVES * 64) void k_ste_gemm(SteGradArgs
             }
         }
     };
-    auto multiply = [&](const GR (&gq)[U], const float2 (&zq)[U], int r, int b) {
+    auto multiply = [&](const float2 (&gq)[U], const float2 (&zq)[U], int r, int b) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (r * RS + my0 + b * U + u < cnt) {
-                const float2 gw = g_wide(gq[u]);
-                if constexpr (kRealG) mfma_step_real(accR, gw.x, zq[u].x);
-                else mfma_step<N>(acc, gw, zq[u], lane);
+                if constexpr (kRealG) mfma_step_real(accR, gq[u].x, zq[u].x);
+                else mfma_step<N>(acc, gq[u], zq[u], lane);
             }
     };
     // scores of the run's steps, KW maps per task: lane l takes step l % RS
@@ -568,9 +558,12 @@ __global__ __launch_bounds__(DictCfg<N>::WAVES * 64) void k_ste_gemm(SteGradArgs
                 // every read next to its use, two round trips a column.
                 // B8 L4096 H32 N128 K64 in bf16 pairs, whole training step:
                 // 3916 -> 3774 us with fences on memory, 3704 with these.
-                // N = 64 with 4 maps a task (B16 L2048 H16 K16) measured
-                // slower this way, 832 -> 846 us; 16 maps at N = 128 have no
-                // registers for two columns.
+                // Over N 8 to 128 and K 17 to 120 (B4 L4096 H8), complex64
+                // and real: N = 128 1.00 and 1.06-1.10x of the step before,
+                // K 48 at N = 64 1.03 and 1.14x (real with its smaller
+                // tiles), elsewhere 0.995-1.01.  N = 64 with 4 maps a task
+                // (B16 L2048 H16 K16) measured slower this way, 832 -> 846
+                // us; 16 maps at N = 128 have no registers for two columns.
                 uint32_t w0[NW4], w1[NW4];
                 TE z0, z1;
                 TE g0[KWD], g1[KWD];
@@ -643,8 +636,7 @@ __global__ __launch_bounds__(DictCfg<N>::WAVES * 64) void k_ste_gemm(SteGradArgs
     // so those loads run during the scores).  Step ids come two runs ahead.
     const int nrun = (cnt + RS - 1) / RS;
     int sid = run_ids(0), sidn = run_ids(1);
-    GR ga[U], gb[U];
-    float2 za[U], zb[U];
+    float2 ga[U], za[U], gb[U], zb[U];
     issue(ga, za, sid, 0);
     issue(gb, zb, sid, 1);
     for (int r = 0; r < nrun; ++r) {
