@@ -1514,8 +1514,9 @@ __device__ __forceinline__ CV<Lay<N>::SL, E> seg_enter_bwd(const FusedArgs& a, c
     return U;
 }
 
-template <int N, int TAU, int W, bool AGG, bool STE, int IO>
-__global__ __launch_bounds__(W * 64) void k_bwd_fused(FusedArgs a) {
+// TWO: registers for two workgroups a CU (see bwd_launch_io).
+template <int N, int TAU, int W, bool AGG, bool STE, int IO, bool TWO = false>
+__global__ __launch_bounds__(W * 64, TWO ? W / 2 : (W + 3) / 4) void k_bwd_fused(FusedArgs a) {
     using E = typename ElemOf<IO>::T;
     constexpr int SL = Lay<N>::SL, LANES = Lay<N>::LANES;
     extern __shared__ __align__(16) unsigned char lds[];
@@ -1595,6 +1596,17 @@ hipError_t bwd_launch_io(const FusedArgs& a, hipStream_t st) {
     }
     // the scaled states for the straight-through gradients come from the scan pass only
     auto kern = a.z ? k_bwd_fused<N, TAU, W, false, true, IO> : k_bwd_fused<N, TAU, W, false, false, IO>;
+    // N = 64 without z in bf16 pairs takes 131 registers, three too many for two
+    // workgroups a CU.  Held to 128 when there are more than a workgroup a CU
+    // (training steps of N 64 K 16: B16 H17 L1000 275 -> 244 us, B16 H32 L100 54
+    // -> 46, B16 H64 L1000 618 -> 601), but not for longer sequences in just two
+    // full rounds of one a CU (B16 H32: L 257 101 -> 97, but L 400 141 -> 142 and
+    // L 1000 298 -> 310).
+    if constexpr (N == 64 && TAU == 8 && W == 8 && IO == kIoBf16) {
+        const int groups = a.B * a.H * a.S;
+        if (!a.z && groups > 256 && (a.C <= 40 || groups != 512))
+            kern = k_bwd_fused<N, TAU, W, false, false, IO, true>;
+    }
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds.total);
     if (e != hipSuccess) return e;

@@ -112,6 +112,18 @@ def test_bf16_io_segmented():
     check(inp, exact, out)
 
 
+@pytest.mark.parametrize("B,L,H", [
+    (16, 100, 17),  # short sequences, more than a workgroup a CU: two share one
+    (16, 321, 32),  # the same, the shortest that does not (41 chunks, 512 workgroups)
+    (16, 321, 17),  # 272 workgroups: a last round that is nearly empty
+])
+def test_bf16_io_many_sequences(B, L, H):
+    inp = make_inputs(B=B, L=L, H=H, N=64, K=9, seed=L + H, with_h0=True, with_dhf=True)
+    exact, out = run_both(inp)
+    assert out["bf"]["chunk"] == 8
+    check(inp, exact, out)
+
+
 @pytest.mark.parametrize("wl", [2, 3])
 def test_bf16_io_full_size(wl):
     inp = workload_inputs(wl, seed=0)
