@@ -317,12 +317,12 @@ def front_bench(args, w, dev):
         "dtype": "bf16 operands, f32 accumulation", "data": "synthetic (seeded)",
         "config": {"workload": w.name + " layer front end", "tokens": T, "d_model": Dm, "H": w.H, "K": w.K,
                    "N": w.N, "step": "dict_argmax+route+project", "parallelism": "single-gpu"},
-        "roofline": {"bound": "mfma", "kernel": "k_project_dma", "achieved": tf, "peak": 2500.0,
+        "roofline": {"bound": "mfma", "kernel": "pdssm_project", "achieved": tf, "peak": 2500.0,
                      "unit": "TFLOP/s", "frac": tf / 2500.0, "traffic": None},
-        "project": {"kernel": "k_project_dma", "ms": pj_ms, "flops": pj_flops, "TFLOPs": tf,
+        "project": {"kernel": "pdssm_project", "ms": pj_ms, "flops": pj_flops, "TFLOPs": tf,
                     "frac_mfma_bf16": tf / 2500.0, "alg_bytes": pj_bytes,
                     "alg_GBps": pj_bytes / (pj_ms * 1e-3) / 1e9, "columns": cols},
-        "route": {"kernel": "k_project_dma (routing tiles only)", "ms": rt_ms, "alg_bytes": rt_bytes,
+        "route": {"kernel": "pdssm_route", "ms": rt_ms, "alg_bytes": rt_bytes,
                   "alg_GBps": rt_bytes / (rt_ms * 1e-3) / 1e9, "flops": rt_flops,
                   "TFLOPs": rt_flops / (rt_ms * 1e-3) / 1e12,
                   "frac_mfma_bf16": rt_flops / (rt_ms * 1e-3) / 1e12 / 2500.0},

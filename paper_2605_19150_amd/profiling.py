@@ -47,6 +47,8 @@ KERNEL_SOURCES = {
     "k_fwd_fused_real": ["pdssm_fused.hip", "pdssm_fused.h", "pdssm_device.h", "pdssm_io.h"],
     "k_bwd_fused_real": ["pdssm_fused.hip", "pdssm_fused.h", "pdssm_device.h", "pdssm_io.h"],
     "k_ste_gemm": ["pdssm_ste.hip", "pdssm_internal.h", "pdssm_device.h", "pdssm_io.h"],
+    "k_project_wide": ["pdssm_select.hip", "pdssm_select.h", "pdssm_project_rule.h", "pdssm_device.h", "pdssm_io.h"],
+    "k_project_thin": ["pdssm_select.hip", "pdssm_select.h", "pdssm_project_rule.h", "pdssm_device.h", "pdssm_io.h"],
 }
 
 
@@ -166,7 +168,9 @@ COUNTER_NOTES = {
     "SQ_WAIT_ANY": "wave-cycles (x4) waiting for anything",
     "SQ_ACTIVE_INST_ANY": "wave-cycles (x4) spent on any instruction",
     "SQ_BUSY_CYCLES": "cycles with active waves in a shader engine",
-    "GRBM_GUI_ACTIVE": "GPU busy cycles",
+    "SQ_VALU_MFMA_BUSY_CYCLES": "cycles the matrix cores are busy, summed over the SIMDs (1024)",
+    "SQ_ACTIVE_INST_VALU": "wave-cycles (x4) spent on VALU instructions",
+    "GRBM_GUI_ACTIVE": "GPU busy cycles, summed over the XCDs (8)",
 }
 
 
