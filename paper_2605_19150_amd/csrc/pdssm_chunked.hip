@@ -1,30 +1,36 @@
-// pdssm_chunked.hip -- chunk-parallel PD scan for gfx950 (three phases).
+// pdssm_chunked.hip -- chunk-parallel PD scan for gfx950 in several passes, for
+// dictionaries beyond LDS.
 //
+// A task is a span of consecutive chunks (at most 64 steps: its choices fill a
+// wave); operators, local terms, carries and U are kept per span, the saved
+// states per chunk.
 // Forward (App. E.1 Algorithm 1, App. E.3 kernels A/B/C, re-designed for
 // 64-lane wavefronts):
-//   k_fwd_agg    one wave per (sequence, chunk): folds the chunk's steps into
+//   k_fwd_agg    one wave per (sequence, span): folds the span's steps into
 //                its PD operator (pi_c, d_c) and local term B_c (state reached
 //                from zero), App. E.3.1 accumulator update.
-//   k_fwd_carry  one wave per sequence: carry_{c+1} = B_c + (pi_c, d_c) carry_c,
-//                storing the state entering every chunk (the saved states).
-//   k_fwd_replay one wave per (sequence, chunk): replays the chunk from its
-//                entering state and reduces the readout y_t on the fly; the
-//                per-step state never leaves the wave.
+//   k_fwd_carry  one wave per sequence: carry_{c+1} = B_c + (pi_c, d_c) carry_c
+//                over the spans, storing the state entering each in U.
+//   k_fwd_replay one wave per (sequence, span): replays the span from its
+//                entering state, writes the state entering every chunk (the
+//                saved states, when the caller wants them) and reduces the
+//                readout y_t on the fly; the per-step state never leaves the
+//                wave.
 // Backward (adjoint of the above; the paper gives no backward scan):
-//   k_bwd_agg    per chunk, in reverse time: the local adjoint gamma_c
-//                (gradient reaching the chunk's entering state from the chunk's
-//                own readouts) and the chunk operator (pi_c, d_c).
-//   k_bwd_carry  per sequence, reverse over chunks:
+//   k_bwd_agg    per span, in reverse time: the local adjoint gamma_c
+//                (gradient reaching the span's entering state from the span's
+//                own readouts) and the span operator (pi_c, d_c).
+//   k_bwd_carry  per sequence, reverse over spans:
 //                U_{c-1} = gamma_c + (pi_c, d_c)^H U_c; U_{-1} = dh0.
-//   k_bwd_emit   per chunk: recomputes the chunk's states from the saved
-//                entering state into LDS, then walks backwards emitting dD, db,
-//                dc.
+//   k_bwd_emit   per span, its chunks from last to first: recomputes a chunk's
+//                states from its saved entering state into LDS, then walks
+//                backwards emitting dD, db, dc.
 //
 // Every scatter-add runs in a fixed order (no float atomics): dictionary steps
 // use the per-entry tables of the prep kernel (source records, or the sorted
 // form for maps with a row of more than kMaxSrc sources), read from the
-// workspace; the carry pass uses the sorted form of every chunk's composed
-// map, built once per chunk by k_fwd_agg.
+// workspace; the carry pass uses the sorted form of every span's composed
+// map, built once per span by k_fwd_agg.
 #include "pdssm_device.h"
 #include "pdssm_internal.h"
 

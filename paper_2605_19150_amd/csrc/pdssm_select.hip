@@ -512,14 +512,15 @@ __global__ __launch_bounds__(512) void k_project_dma(ProjectArgs a) {
 // weights' rows are permuted in LDS so that a pair's two columns fall to one
 // lane) without staging or waiting.
 //
-// Bound: the matrix cores at the clock that the card's power limit leaves
-// (about 1.8 GHz of 2.4 with normal data); of the cycles of a launch at
-// hybrid-lm, 66% are matrix instructions' own, 14% the barriers and operand
-// reads, 9% the loads and 11% the epilogue.  Measured against eight waves with
-// slices of 32: B8 L4096 d 4096, 26624 columns 8150 -> 5700 us (1250 TFLOP/s;
-// the vendor library's plain bf16 product of these sizes 1520), B16 L2048
-// d 1024, 6400 columns 640 -> 480 us.  Without the L2 prefetch the former
-// takes 8% more; with loads issued two at a time 5% more.
+// Bound: the matrix cores at the clock that the card leaves them.  At 32768
+// tokens, d 4096, 26624 columns a launch takes 1.0e7 cycles (1.76 GHz), the
+// matrix cores are busy for 68% of them and the waves wait for 16%; no LDS bank
+// conflicts; 10.7 GB fetched (u and the weights are 0.5 GB) and 3.2 GB written.
+// At d 1024, 6400 columns 45% and 16%.  Measured against eight waves with slices
+// of 32 (k_project_dma<256>), in turn on one box: 8068 -> 5792 us (1234 TFLOP/s)
+// and 625 -> 473 us (908 TFLOP/s); the vendor library's plain bf16 products with
+// bf16 outputs of these sizes take 4620 and 354 us.  Without the L2 prefetch
+// the former takes 5.5% more, the latter 1% less, d 64 3% less.
 struct WideProj {
     static constexpr int BM = 256, BN = 256, BK = 64;
     static constexpr int ROWB = BK * 2;           // bytes of a row's slice: one 128-byte line
