@@ -1256,12 +1256,14 @@ hipError_t project_wide_launch(const ProjectArgs& a, hipStream_t st) {
 template <int TB, int NS>
 hipError_t project_thin_run(const ProjectArgs& a, int blocks, int waves, hipStream_t st) {
     using C = ThinProj<TB, NS>;
-    const int lds = waves * C::WAVE;  // at most 160 KB by the callers' choice of NS
+    // the most any launch of this kernel takes: the same from every thread
+    constexpr int kMost = (4 * C::WAVE <= 160 * 1024 ? 4 : 2) * C::WAVE;
+    static_assert(kMost <= 160 * 1024, "fits the LDS of a CU");
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_project_thin<TB, NS>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kMost);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_project_thin<TB, NS>), dim3((unsigned)blocks, (unsigned)((a.T + C::TT - 1) / C::TT)),
-                       dim3(64 * waves), lds, st, a);
+                       dim3(64 * waves), waves * C::WAVE, st, a);
     return hipGetLastError();
 }
 
