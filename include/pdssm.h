@@ -167,7 +167,9 @@ size_t pdssm_workspace_size(const pdssm_desc* desc, int op);
 
 /* 1 if the scans of desc run the single-read kernels (one head's dictionary
  * tables fit in LDS), 0 if they run the multi-pass kernels, or a negative
- * status for an invalid desc. */
+ * status for an invalid desc.  The latter cut each sequence into spans of at
+ * most 64 steps whose operators are composed; the span, as the segments below,
+ * depends on B*H and L, and with it the last bits of the results. */
 int pdssm_uses_fused(const pdssm_desc* desc);
 
 /* Number of segments each sequence is cut into along L by the single-read
@@ -194,9 +196,9 @@ const char* pdssm_status_string(int status);
  * before them on the same stream or ordered before them by the caller.
  * An entry of pi outside [0,N) is reported through *dev_status here.
  * ws: at least pdssm_workspace_size(desc, PDSSM_OP_FWD) bytes (the forward and
- * backward sizes are equal), 256-byte aligned, not overlapping pi.  When the
- * scans of desc run the chunked kernels (dictionaries too large for LDS) no
- * tables are needed and the call enqueues nothing.
+ * backward sizes are equal), 256-byte aligned, not overlapping pi.  The
+ * multi-pass kernels (dictionaries too large for LDS) read the same tables,
+ * from ws.
  */
 int pdssm_prepare(const pdssm_desc* desc, const int32_t* pi, void* ws, size_t ws_bytes,
                   int* dev_status, void* stream);
